@@ -8,8 +8,8 @@
 // sequence) streams its keys and values once for all G query heads of the
 // group, and the sequence's keys are split evenly over its workgroups, about as
 // many workgroups in all as the chip holds at once (with at most 64 sequences,
-// the grid's sequence rows take the sequences longest first).  bf16 caches take the
-// scores of 16 keys at a time from matrix-core products (decode_partial_bf16_kernel);
+// the grid's sequence rows take the sequences longest first).  bf16 caches run both
+// contractions on the matrix cores, 32 keys at a time (decode_partial_bf16_kernel);
 // float32 caches take a 16-byte chunk of a key row per lane with scores reduced
 // across the lanes of a row by DPP lane permutations (decode_partial_kernel).
 // Both keep an online softmax in float32 that rescales only when a running
@@ -32,9 +32,6 @@ namespace {
 #endif
 #ifndef PRCR_DEC_WORKGROUPS
 #define PRCR_DEC_WORKGROUPS 0    // workgroups per call; 0: as many as are resident at once
-#endif
-#ifndef PRCR_DEC_MFMA
-#define PRCR_DEC_MFMA 1
 #endif
 #ifndef PRCR_DEC_WAVES
 #define PRCR_DEC_WAVES 4
@@ -336,18 +333,31 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
 }
 
 // ---------------------------------------------------------------------------
-// bf16 caches: the scores of a tile of 16 keys come from one matrix-core product
-// per 32 elements of the head dim, K(16 keys) x Q(query rows)^T, with float32
-// accumulation.  The float32 query of each head is split into three bf16 parts
-// (the leading 8 significant bits, then the next 8 of what is left, then the
-// rest), whose sum is exactly the float32 value, and the parts are rows of the
-// product, so a key's score is the sum of its three part scores: as exact as a
-// float32 dot product.  The softmax runs once per key in the lanes that hold the
-// key's scores, with a running maximum shared by the wave, and the weights reach
-// the lanes that hold the key's value row through LDS.
+// bf16 caches: both contractions of a tile of 32 keys run on the matrix cores,
+// with float32 accumulation and no precision given up to the 16-bit operands.
+//
+//   scores   K(16 keys) x Q^T: the float32 query of each head is split into three
+//            bf16 parts (the leading 8 significant bits, the next 8 of what is
+//            left, then the rest) whose sum is exactly the float32 value.  Row
+//            4 h + part of the query operand is part `part` of head h, so that a
+//            lane ends with the three part scores of one (head, key) in its own
+//            accumulators and adds them: a float32 dot product's accuracy.
+//   values   P x V: the float32 weights are split into three bf16 parts in the
+//            same way and are rows of the product, so that each output feature is
+//            the sum of three rows, again exact products with float32 sums.
+//
+// The vector ALU is left with the softmax (one exponential per head and key,
+// spread over all 64 lanes) and the transpose of the value rows (one byte
+// permutation per two elements, in registers), at the same cost for 1 to 4 and for
+// 5 to 8 query heads per KV head.  What bounds the kernel is reading the cache.
+// With the weighted value sum on the vector ALU (a multiply-add per element and
+// head, 16-key tiles) a layer of 64 paged sequences of 2,912-6,512 keys, 4 KV heads
+// and 7 query heads each took 169.6 us, now 123.5 (619 MB); 32 contiguous sequences
+// of 2,756-4,256 keys, 8 KV heads and 4 query heads each 81.7, now 79.7 (458 MB).
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ f32x4 mfma_16x16x32(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
@@ -382,38 +392,62 @@ __device__ __forceinline__ float row_max16(float s) {
   return s;
 }
 
-// kTileBlocks (paged only): block_size is a multiple of 16, so that every tile
-// of 16 keys (tiles start at multiples of 16) lies in one block.
-template <int D, int GT, bool kPaged, bool kTileBlocks>
-__global__ __launch_bounds__(kWaves * kWave, GT >= 8 ? 2 : 3) void decode_partial_bf16_kernel(const DecodeParams p) {
-  constexpr int kTile = 16;                  // keys per wave and tile: the product's N
-  constexpr int KK = D / 32;                 // products over the head dim per query row tile
-  constexpr int kRows = 3 * GT;              // query rows: three parts of every head
-  constexpr int kATiles = (kRows + 15) / 16; // 16-row query tiles
-  constexpr int kXS = kATiles * 16 + 4;      // floats per key in the part-score exchange (padded)
-  constexpr int EPL = Elems<uint16_t>::kPerChunk;   // value elements per lane (one 16-byte chunk)
-  constexpr int LPK = D / EPL;               // lanes per value row
-  constexpr int KPW = kWave / LPK;           // value rows per load
-  constexpr int VL = kTile / KPW;            // value loads per lane and tile
+// Upper halves of two words (a's in the low half of the result), and lower halves.
+__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) {
+  return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+__device__ __forceinline__ uint32_t pack_lo(uint32_t a, uint32_t b) {
+  return __builtin_amdgcn_perm(b, a, 0x05040100u);
+}
+
+// A lane's share of one value row: 16 bytes (head_dim 128) or 8 (head_dim 64).
+template <int kWords>
+struct Words;
+template <>
+struct Words<4> {
+  typedef uint32_t type __attribute__((ext_vector_type(4)));
+};
+template <>
+struct Words<2> {
+  typedef uint32_t type __attribute__((ext_vector_type(2)));
+};
+
+constexpr int kTile = 32;   // keys per wave and tile: the value product's contraction length
+
+// GT: query heads per KV head the kernel has room for (4 or 8; smaller groups
+// repeat their first head).  kHalfBlocks (paged only): block_size is a multiple of
+// 16, so that each half of a tile (tiles start at multiples of 32) lies in one
+// block; other block sizes look every key up.
+template <int D, int GT, bool kPaged, bool kHalfBlocks>
+__global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void decode_partial_bf16_kernel(const DecodeParams p) {
+  constexpr int KK = D / 32;                 // products over the head dim per 16 keys
+  constexpr int kA = GT / 4;                 // query operands: 4 heads x (3 parts + 1 unused row)
+  constexpr int kPT = GT / 4;                // weight operands of 16 rows (below)
+  constexpr int kPRows = 3 * GT + (GT == 4 ? 4 : 0);   // weight rows in LDS
+  constexpr int kDL = D / 16;                // value elements per lane and row
+  constexpr int kVW = kDL / 2;               // 32-bit words of them
+  constexpr int kVL = kTile / 4;             // value loads per lane and tile (4 rows each)
   constexpr int kRowBytes = D * 2;
   constexpr int KPB = kWaves * kTile;        // keys per workgroup per round of tiles
   constexpr int P = D / 2;
-  static_assert(KK >= 1 && D % 32 == 0 && VL >= 1, "unsupported head_dim");
+  // Weight rows in LDS: 32 keys of bf16, padded so that the 16 rows an operand
+  // read touches at once fall on different banks.
+  constexpr int kPS = kTile / 2 + 4;         // words per row
+  typedef typename Words<kVW>::type vrow;
+  static_assert(GT == 4 || GT == 8, "unsupported group");
+  static_assert(D == 64 || D == 128, "unsupported head_dim");
   __shared__ __align__(16) float s_q[GT][D];
-  __shared__ __align__(16) float s_x[kWaves][kTile][kXS];
-  __shared__ __align__(16) float s_p[kWaves][kTile][GT];
+  __shared__ __align__(16) uint32_t s_p[kWaves][kPRows][kPS];
   __shared__ float s_m[kWaves][GT];
   __shared__ float s_l[kWaves][GT];
-  __shared__ float s_o[kWaves][GT][D];
+  __shared__ __align__(16) float s_o[kWaves][16][D];
 
   const int split = blockIdx.x, kvh = blockIdx.y;
   const int lane = threadIdx.x & (kWave - 1);
   const int b = sequence_of_row(p, lane, blockIdx.z);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int kt = lane % kTile;               // key of the tile whose scores this lane holds
-  const int kj = lane / kTile;               // 16-byte chunks 4*kk + kj of that key's row
-  const int vr = lane / LPK;                 // value row slot within a load
-  const int vc = lane % LPK;                 // 16-byte chunk of the value row
+  const int n16 = lane % 16;                 // product column; operand row
+  const int kj = lane / 16;                  // k group of the operands; head of the lane's scores
   const int G = p.n_q_heads / p.n_kv_heads;
 
   const int64_t cap = kPaged ? static_cast<int64_t>(p.max_blocks) * p.block_size : p.s_max;
@@ -425,7 +459,7 @@ __global__ __launch_bounds__(kWaves * kWave, GT >= 8 ? 2 : 3) void decode_partia
   }
   const int per = (len + p.n_split - 1) / p.n_split;
   const int chunk = (per + KPB - 1) / KPB * KPB;
-  const int j0 = min(len, split * chunk);
+  const int j0 = static_cast<int>(min(static_cast<int64_t>(len), static_cast<int64_t>(split) * chunk));
   const int j1 = min(len, j0 + chunk);
 
   // Rotated, scaled query of every head of the group (pair i with i + D/2, the
@@ -445,236 +479,294 @@ __global__ __launch_bounds__(kWaves * kWave, GT >= 8 ? 2 : 3) void decode_partia
       s_q[g][i + P] = static_cast<float>((xp * cs + x * sn) * qs);
     }
   }
+  // Weight rows: the three parts of head h are rows h, 4 + h and 8 + h (4 heads; rows
+  // 12..15 are not used), or h, 8 + h and 16 + h (8 heads: the first operand holds rows
+  // 0..15, the second adds rows 16..23 to the first eight rows' sums).
   __syncthreads();
-  // Query operand: row r = 16a + lane%16 of tile a is part r / GT of head r % GT;
-  // the lane's 8 elements of product kk are those of row chunk 4*kk + kj, the
-  // same chunk as the key operand below.
-  u32x4 qa[kATiles][KK];
+  // Query operands: row n16 of operand a is part n16 % 4 of head 4 a + n16 / 4 (a
+  // fourth part is zero); the lane's 8 elements of product kk are those of row
+  // chunk 4 kk + kj, the same chunk as the key operand below.
+  u32x4 qa[kA][KK];
 #pragma unroll
-  for (int a = 0; a < kATiles; ++a) {
-    const int r = 16 * a + kt;
+  for (int a = 0; a < kA; ++a) {
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       u32x4 w = {0u, 0u, 0u, 0u};
-      if (r < kRows) {
-        const int part = r / GT, g = r % GT;
-        const float *src = &s_q[g][8 * (4 * kk + kj)];
+      const int part = n16 % 4;
+      if (part < 3) {
+        const float *src = &s_q[4 * a + n16 / 4][8 * (4 * kk + kj)];
 #pragma unroll
         for (int h = 0; h < 4; ++h)
-          w[h] = (split_part(src[2 * h], part) >> 16) | (split_part(src[2 * h + 1], part) & 0xFFFF0000u);
+          w[h] = pack_hi(split_part(src[2 * h], part), split_part(src[2 * h + 1], part));
       }
       qa[a][kk] = w;
     }
   }
 
-  const int64_t row_base = kPaged ? 0
-                                  : ((static_cast<int64_t>(b) * p.n_layers + p.layer) * p.n_kv_heads + kvh) * p.s_max;
-  const int64_t row_any = kPaged ? static_cast<int64_t>(p.layer) * p.n_blocks * p.block_size * p.n_kv_heads + kvh
-                                 : row_base;
+  // Keys of a tile.  Column n16 of score product st is key 8 (n16/4) + 4 st + n16%4,
+  // value load u holds key 4 u + kj: both put key t at position (t % 4) * 8 + t / 4
+  // of the value product's contraction, with a lane's two scores in one word.
+  const int kt0 = 8 * (n16 / 4) + n16 % 4;
+  const int64_t row_layer = static_cast<int64_t>(p.layer) * p.n_blocks * p.block_size;   // paged
+  const int64_t row_any = kPaged ? row_layer * p.n_kv_heads + kvh
+                                 : ((static_cast<int64_t>(b) * p.n_layers + p.layer) * p.n_kv_heads + kvh) * p.s_max;
+  const char *const cache_k = static_cast<const char *>(p.cache_k);
+  const char *const cache_v = static_cast<const char *>(p.cache_v);
   int bad_block = 0;
-  // Block-table entry of key j (the sequence's first entry past the chunk).
-  auto table = [&](int j) -> int32_t {
-    const int js = j < j1 ? j : 0;
-    const int lb = p.block_shift >= 0 ? (js >> p.block_shift) : js / p.block_size;
-    return p.block_table[static_cast<int64_t>(b) * p.max_blocks + lb];
+
+  // Block-table entry of key `lane % 32` of the tile at tb (the sequence's first
+  // entry past the chunk), and that key's offset in its block.  Entries are read
+  // two tiles ahead, so that the loads that need one never wait for it.
+  struct Entry {
+    int32_t blk, off;
   };
-  // Addressing.  Contiguous caches and whole-tile blocks address a tile by its
-  // first row and the stride between its keys' rows (1 row, or n_kv_heads rows
-  // within a block); other paged caches read a block-table entry per key.  Keys
-  // at or past `lim`, or in a block outside the pool, read row_any instead (every
-  // load is issued unconditionally) and are marked dead: they get no weight,
-  // and their values are taken as zero.
-  struct TileAddr {
-    int64_t base;
-    bool ok;
+  auto entry_of = [&](int tb) -> Entry {
+    Entry e{0, 0};
+    if constexpr (kPaged) {
+      const int j = tb + lane % kTile;
+      const int js = j < j1 ? j : 0;
+      const int lb = p.block_shift >= 0 ? (js >> p.block_shift) : js / p.block_size;
+      e.blk = p.block_table[static_cast<int64_t>(b) * p.max_blocks + lb];
+      e.off = js - lb * p.block_size;
+    }
+    return e;
   };
-  auto tile_addr = [&](int tb, int32_t blk) -> TileAddr {
-    if constexpr (kTileBlocks) {
-      const int lb = p.block_shift >= 0 ? (tb >> p.block_shift) : tb / p.block_size;
-      const bool ok = blk >= 0 && blk < p.n_blocks;
-      return {((static_cast<int64_t>(p.layer) * p.n_blocks + blk) * p.block_size + (tb - lb * p.block_size)) *
-                      p.n_kv_heads + kvh, ok};
+  // Rows of a tile.  Every load is issued unconditionally: keys past the chunk, or
+  // in a block outside the pool, read a row that exists and are left out of `live`
+  // (bit t: key t); they get no weight, and their values are taken as zero.
+  //   contiguous     one base; key t is row min(t, last)
+  //   half blocks    one base per half; key t is row min(t % 16, last[t / 16])
+  //   other blocks   lane t holds key t's slot in the layer's pool (below 2^32: a
+  //                  pool's slots are at least 128 bytes each)
+  struct TileRows {
+    int64_t base[2];
+    int last[2];
+    uint32_t slot;
+    uint32_t live;
+  };
+  auto rows_of = [&](int tb, Entry e) -> TileRows {
+    TileRows t{};
+    const int n_in = min(max(j1 - tb, 0), kTile);
+    t.live = n_in >= kTile ? ~0u : (1u << n_in) - 1u;
+    if constexpr (!kPaged) {
+      const int tc = min(tb, j1 - 1);
+      t.base[0] = row_any + tc;
+      t.last[0] = j1 - 1 - tc;
     } else {
-      return {row_base + tb, true};
+      const bool in = (t.live >> (lane % kTile)) & 1u;
+      const bool ok = in && e.blk >= 0 && e.blk < p.n_blocks;
+      const uint32_t live = static_cast<uint32_t>(__ballot(ok));   // lanes t and t + 32 agree
+      bad_block |= live != t.live;
+      t.live = live;
+      const int64_t slot = static_cast<int64_t>(e.blk) * p.block_size + e.off;
+      if constexpr (kHalfBlocks) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t lh = (live >> (16 * h)) & 0xFFFFu;
+          const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(slot), 16 * h);
+          const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(slot >> 32), 16 * h);
+          const int64_t s = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+          t.base[h] = lh != 0 ? (row_layer + s) * p.n_kv_heads + kvh : row_any;
+          t.last[h] = lh != 0 ? __popc(lh) - 1 : 0;
+        }
+      } else {
+        t.slot = ok ? static_cast<uint32_t>(slot) : 0u;
+      }
+    }
+    return t;
+  };
+  const uint32_t row_step = kPaged ? static_cast<uint32_t>(p.n_kv_heads) * kRowBytes : kRowBytes;
+  // Byte offset of key t (t / 16 == half).
+  auto key_offset = [&](const TileRows &tr, int t, int half) -> int64_t {
+    if constexpr (!kPaged)
+      return tr.base[0] * kRowBytes + static_cast<uint32_t>(min(t, tr.last[0])) * row_step;
+    else if constexpr (kHalfBlocks)
+      return tr.base[half] * kRowBytes + static_cast<uint32_t>(min(t - 16 * half, tr.last[half])) * row_step;
+    else
+      return (row_layer + static_cast<int64_t>(static_cast<uint32_t>(__shfl(static_cast<int>(tr.slot), t)))) *
+                 row_step + static_cast<int64_t>(kvh) * kRowBytes;
+  };
+  // Key rows in the product's operand layout.  A load reads a quarter of each of 16
+  // rows and the other quarters follow at once from the same cache lines, so these
+  // are plain loads: as non-temporal loads they took 10 % longer.
+  auto load_k = [&](const TileRows &tr, u32x4 (&kd)[2][KK]) {
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      const int t = kt0 + 4 * st;
+      int64_t o;
+      if constexpr (kPaged && kHalfBlocks)
+        o = n16 < 8 ? key_offset(tr, t, 0) : key_offset(tr, t, 1);
+      else
+        o = key_offset(tr, t, 0);
+      const char *kp = cache_k + o + kj * 16;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) kd[st][kk] = *reinterpret_cast<const u32x4 *>(kp + kk * 64);
     }
   };
-  constexpr int kStrideHeads = kPaged ? 1 : 0;   // rows between keys: n_kv_heads (paged) or 1
-  auto key_row = [&](int tb, const TileAddr &ta, int t, int lim, bool &live) -> int64_t {
-    const int j = tb + t;
-    const bool in = j < lim;
-    if constexpr (kPaged && !kTileBlocks) {
-      const int32_t blk = table(j);
-      const bool ok = blk >= 0 && blk < p.n_blocks;
-      bad_block |= in && !ok;
-      live = in && ok;
-      const int lb = p.block_shift >= 0 ? (j >> p.block_shift) : j / p.block_size;
-      const int64_t row = ((static_cast<int64_t>(p.layer) * p.n_blocks + blk) * p.block_size + (j - lb * p.block_size)) *
-                              p.n_kv_heads + kvh;
-      return live ? row : row_any;
-    } else {
-      bad_block |= in && !ta.ok;
-      live = in && ta.ok;
-      const int64_t row = ta.base + static_cast<int64_t>(t) * (kStrideHeads ? p.n_kv_heads : 1);
-      return live ? row : row_any;
+  // Value rows, 16 lanes to a row.
+  auto load_v = [&](const TileRows &tr, vrow (&vd)[kVL]) {
+#pragma unroll
+    for (int u = 0; u < kVL; ++u) {
+      const int64_t o = key_offset(tr, 4 * u + kj, u / 4);
+      vd[u] = __builtin_nontemporal_load(reinterpret_cast<const vrow *>(cache_v + o + n16 * (kDL * 2)));
     }
-  };
-  // Key rows of a tile in the product's operand layout.  A load reads a quarter
-  // of each of 16 rows and the other quarters follow at once from the same cache
-  // lines, so these are plain loads: as non-temporal loads they took 10 % longer.
-  auto load_k = [&](int tb, const TileAddr &ta, int lim, u32x4 *kd, bool &kl) {
-    const int64_t rk = key_row(tb, ta, kt, lim, kl);
-    const char *kp = static_cast<const char *>(p.cache_k) + rk * kRowBytes + kj * 16;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-      kd[kk] = *reinterpret_cast<const u32x4 *>(kp + kk * 64);
-  };
-  // Value rows of a tile, 16 lanes to a row.
-  auto load_v = [&](int tb, const TileAddr &ta, int lim, u32x4 *vd, bool *vl) {
-    int64_t rv[VL];
-#pragma unroll
-    for (int u = 0; u < VL; ++u) rv[u] = key_row(tb, ta, KPW * u + vr, lim, vl[u]);
-#pragma unroll
-    for (int u = 0; u < VL; ++u)
-      vd[u] = load_nt(static_cast<const char *>(p.cache_v) + rv[u] * kRowBytes + vc * 16);
   };
 
-  float o[GT][EPL], lsum[GT], mrun[GT];
+  f32x4 acc[kDL];                            // rows 4 kj + r, features kDL * n16 + dt
 #pragma unroll
-  for (int g = 0; g < GT; ++g) {
-    lsum[g] = 0.f;
-    mrun[g] = -FLT_MAX;
+  for (int dt = 0; dt < kDL; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float mrun[kA], lsum[kA];                  // head 4 a + kj; lsum over the lane's own keys
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) o[g][e] = 0.f;
+  for (int a = 0; a < kA; ++a) {
+    mrun[a] = -FLT_MAX;
+    lsum[a] = 0.f;
   }
 
-  // The wave's tiles start at jw + n*KPB.  With whole-tile blocks the wave reads
-  // the block-table entries of 64 tiles at once, one per lane, and takes each
-  // from its lane when the tile comes; the keys of the next 64 tiles are then a
-  // new round (its first tile loaded again; keys from `lim` on are dead here).
-  //
-  // One buffer per operand, software-pipelined: the next tile's key rows are
-  // loaded once this tile's product has read them, and its value rows once this
-  // tile's weighted sum has; each load's latency hides behind the other half of
-  // a tile's work, and every wait is for the oldest loads only.
+  // The wave's tiles start at jw + n * KPB.  One buffer per operand, software
+  // pipelined: the next tile's key rows are loaded once this tile's products have
+  // read them, and its value rows once the value product has; each load's latency
+  // hides behind the other half of a tile's work.
   const int jw = j0 + wave * kTile;
-  // Rounds of 64 tiles with whole-tile blocks; one round otherwise (lim = j1).
-  const int n_tiles = jw < j1 ? (j1 - jw + KPB - 1) / KPB : 0;
-  const int rounds = kTileBlocks ? (n_tiles + kWave - 1) / kWave : (n_tiles > 0 ? 1 : 0);
-  for (int r = 0; r < rounds; ++r) {
-    const int n0 = r * kWave;
-    int32_t tab_lane = 0;
-    if constexpr (kTileBlocks) tab_lane = table(jw + (n0 + lane) * KPB);
-    const int lim = kTileBlocks ? static_cast<int>(min(static_cast<int64_t>(j1),
-                                                       static_cast<int64_t>(jw) + static_cast<int64_t>(n0 + kWave) * KPB))
-                                : j1;
-    auto addr_of = [&](int n) -> TileAddr {
-      const int tb = jw + n * KPB;
-      int32_t blk = 0;
-      if constexpr (kTileBlocks) blk = __builtin_amdgcn_readlane(tab_lane, min(n - n0, kWave - 1));
-      return tile_addr(tb, blk);
-    };
-    u32x4 kr[KK], vv[VL];
-    bool kl, vl[VL];
-    int n = n0, jt = jw + n0 * KPB;
-    TileAddr ta = addr_of(n);
-    load_k(jt, ta, lim, kr, kl);
-    load_v(jt, ta, lim, vv, vl);
-    while (jt < lim) {
-      const TileAddr ta_n = addr_of(n + 1);
-      // Part scores: lane holds rows 16a + 4*(lane/16) + i of the product for key kt.
-      f32x4 acc[kATiles];
+  if (jw < j1) {
+    u32x4 kr[2][KK];
+    vrow vv[kVL];
+    Entry e_next;
+    TileRows tr;
+    {
+      const Entry e0 = entry_of(jw);
+      e_next = entry_of(jw + KPB);
+      tr = rows_of(jw, e0);
+    }
+    load_k(tr, kr);
+    load_v(tr, vv);
+    for (int jt = jw; jt < j1; jt += KPB) {
+      const uint32_t live = tr.live;
+      f32x4 sa[kA][2];
 #pragma unroll
-      for (int a = 0; a < kATiles; ++a) {
-        acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int a = 0; a < kA; ++a) {
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) acc[a] = mfma_16x16x32(qa[a][kk], kr[kk], acc[a]);
+        for (int st = 0; st < 2; ++st) {
+          sa[a][st] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk) sa[a][st] = mfma_16x16x32(qa[a][kk], kr[st][kk], sa[a][st]);
+        }
       }
-      bool kl_n;
-      load_k(jt + KPB, ta_n, lim, kr, kl_n);
-#pragma unroll
-      for (int a = 0; a < kATiles; ++a) {
-        const int r0 = 16 * a + 4 * kj;
-        if (r0 < kRows) *reinterpret_cast<f32x4 *>(&s_x[wave][kt][r0]) = acc[a];
-      }
-      wave_lds_sync();
-      // Every row of 16 lanes now takes the same 16 keys: lane kt's key, all heads.
-      float sc[GT];
+      // (A tile past the chunk re-reads one row.)
+      tr = rows_of(jt + KPB, e_next);
+      e_next = entry_of(jt + 2 * KPB);
+      load_k(tr, kr);
+
+      const bool live0 = (live >> kt0) & 1u, live1 = (live >> (kt0 + 4)) & 1u;
+      float sc[kA][2];
       bool rise = false;
 #pragma unroll
-      for (int g = 0; g < GT; ++g) {
-        const float s = (s_x[wave][kt][g] + s_x[wave][kt][GT + g]) + s_x[wave][kt][2 * GT + g];
-        sc[g] = kl ? s : -FLT_MAX;
-        rise = rise || sc[g] > mrun[g];
+      for (int a = 0; a < kA; ++a) {
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+          const float s = (sa[a][st][0] + sa[a][st][1]) + sa[a][st][2];
+          sc[a][st] = (st == 0 ? live0 : live1) ? s : -FLT_MAX;
+          rise = rise || sc[a][st] > mrun[a];
+        }
       }
       // The tile's maxima are needed only when some score rose above the running
       // maximum of its head (rarely, after the first tiles).
       if (__any(rise)) {
+        float corr[kA];
 #pragma unroll
-        for (int g = 0; g < GT; ++g) {
-          const float tmax = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(row_max16(sc[g]))));
-          const float mnew = fmaxf(mrun[g], tmax);
-          const float corr = exp2_fast(mrun[g] - mnew);
-          lsum[g] *= corr;
+        for (int a = 0; a < kA; ++a) {
+          const float mnew = fmaxf(mrun[a], row_max16(fmaxf(sc[a][0], sc[a][1])));
+          corr[a] = exp2_fast(mrun[a] - mnew);
+          lsum[a] *= corr[a];
+          mrun[a] = mnew;
+        }
+        // Accumulator row 4 kj + r belongs to head r (4 heads), or to head
+        // 4 (kj % 2) + r (8 heads); head h's factor is in lanes 16 (h % 4)...
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) o[g][e] *= corr;
-          mrun[g] = mnew;
+        for (int r = 0; r < 4; ++r) {
+          float c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(corr[0]), 16 * r));
+          if constexpr (kA == 2) {
+            const float c1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(corr[kA - 1]), 16 * r));
+            c = (kj & 1) ? c1 : c;
+          }
+#pragma unroll
+          for (int dt = 0; dt < kDL; ++dt) acc[dt][r] *= c;
         }
       }
-      float pw[GT];
+      // Weights and their three bf16 parts, two keys to a word.  A part that is zero
+      // is raised to the smallest normal bf16 when the weight is not (2^-126, where the
+      // chunk's largest weight is 1): a zero part times an infinite value would make a NaN where
+      // weight times value is infinite.
 #pragma unroll
-      for (int g = 0; g < GT; ++g) {
-        pw[g] = exp2_fast(sc[g] - mrun[g]);
-        lsum[g] += pw[g];
-      }
-      if (lane < kTile) {
+      for (int a = 0; a < kA; ++a) {
+        uint32_t part[3][2];
 #pragma unroll
-        for (int g = 0; g < GT; ++g) s_p[wave][kt][g] = pw[g];
+        for (int st = 0; st < 2; ++st) {
+          const float w = (st == 0 ? live0 : live1) ? exp2_fast(sc[a][st] - mrun[a]) : 0.f;
+          lsum[a] += w;
+          const uint32_t tiny = w > 0.f ? 0x00800000u : 0u;
+#pragma unroll
+          for (int q = 0; q < 3; ++q) part[q][st] = max(split_part(w, q), tiny);
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const int row = GT == 4 ? 4 * q + kj : 8 * q + 4 * a + kj;
+          s_p[wave][row][(n16 % 4) * 4 + n16 / 4] = pack_hi(part[q][0], part[q][1]);
+        }
       }
       wave_lds_sync();
-      // A zero weight times a value read from another row could make a NaN:
-      // values of keys without weight are taken as zero.
+      u32x4 pa[kPT];
+      pa[0] = *reinterpret_cast<const u32x4 *>(&s_p[wave][n16][4 * kj]);
+      if constexpr (kPT == 2) {
+        // The second operand's other eight rows add to the middle parts' sums: they
+        // repeat its weights cut to the smallest normal value (for the reason above).
+        pa[kPT - 1] = *reinterpret_cast<const u32x4 *>(&s_p[wave][16 + n16 % 8][4 * kj]);
+        const u16x2 most = __builtin_bit_cast(u16x2, n16 < 8 ? 0xFFFFFFFFu : 0x00800080u);
 #pragma unroll
-      for (int u = 0; u < VL; ++u) {
-        const int tk = KPW * u + vr;
-        float v[EPL];
-        Elems<uint16_t>::unpack(vl[u] ? vv[u] : u32x4{0u, 0u, 0u, 0u}, v);
+        for (int w = 0; w < 4; ++w)
+          pa[kPT - 1][w] = __builtin_bit_cast(
+              uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, pa[kPT - 1][w]), most));
+      }
+      // A zero weight times a value read from another row could make a NaN: values
+      // of keys without weight are taken as zero.
+      if (live != ~0u) {
 #pragma unroll
-        for (int g = 0; g < GT; ++g) {
-          const float w = s_p[wave][tk][g];
+        for (int u = 0; u < kVL; ++u) {
+          const uint32_t keep = (live >> (4 * u + kj)) & 1u ? ~0u : 0u;
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) o[g][e] = fmaf(w, v[e], o[g][e]);
+          for (int w = 0; w < kVW; ++w) vv[u][w] &= keep;
         }
       }
-      load_v(jt + KPB, ta_n, lim, vv, vl);
-      kl = kl_n;
-      jt += KPB;
-      ++n;
-    }
-  }
-  if (bad_block && p.err != nullptr) atomicOr(p.err, PRCR_DERR_BLOCK);
-
-  // Every lane of the wave used the same running maxima: the value row slots add
-  // up plainly, and so do the weight sums of the 16 keys of a row of lanes.
+      // Transposed value operand: feature kDL * n16 + dt of the lane's 8 keys.
 #pragma unroll
-  for (int off = LPK; off < kWave; off <<= 1) {
+      for (int dt = 0; dt < kDL; ++dt) {
+        u32x4 vb;
 #pragma unroll
-    for (int g = 0; g < GT; ++g) {
+        for (int w = 0; w < 4; ++w)
+          vb[w] = dt % 2 == 0 ? pack_lo(vv[2 * w][dt / 2], vv[2 * w + 1][dt / 2])
+                              : pack_hi(vv[2 * w][dt / 2], vv[2 * w + 1][dt / 2]);
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) o[g][e] += __shfl_xor(o[g][e], off);
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < GT; ++g) lsum[g] = group_sum<16>(lsum[g]);
-  if (lane < LPK) {
-#pragma unroll
-    for (int g = 0; g < GT; ++g) {
-      if (lane == 0) {
-        s_m[wave][g] = mrun[g];
-        s_l[wave][g] = lsum[g];
+        for (int q = 0; q < kPT; ++q) acc[dt] = mfma_16x16x32(pa[q], vb, acc[dt]);
       }
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) s_o[wave][g][vc * EPL + e] = o[g][e];
+      load_v(tr, vv);
     }
+  }
+  if (bad_block && lane == 0 && p.err != nullptr) atomicOr(p.err, PRCR_DERR_BLOCK);
+
+  // The lanes of a row of 16 hold different keys of one head.
+#pragma unroll
+  for (int a = 0; a < kA; ++a) {
+    lsum[a] = group_sum<16>(lsum[a]);
+    if (n16 == 0) {
+      s_m[wave][4 * a + kj] = mrun[a];
+      s_l[wave][4 * a + kj] = lsum[a];
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+#pragma unroll
+    for (int c = 0; c < kDL / 4; ++c)
+      *reinterpret_cast<f32x4 *>(&s_o[wave][4 * kj + r][kDL * n16 + 4 * c]) =
+          f32x4{acc[4 * c][r], acc[4 * c + 1][r], acc[4 * c + 2][r], acc[4 * c + 3][r]};
   }
   __syncthreads();
   for (int idx = threadIdx.x; idx < G * D; idx += kWaves * kWave) {
@@ -685,7 +777,9 @@ __global__ __launch_bounds__(kWaves * kWave, GT >= 8 ? 2 : 3) void decode_partia
     for (int w = 0; w < kWaves; ++w) {
       const float wt = exp2_fast(s_m[w][g] - M);
       Ls += s_l[w][g] * wt;
-      Os += s_o[w][g][d] * wt;
+      const float o = GT == 4 ? (s_o[w][g][d] + s_o[w][4 + g][d]) + s_o[w][8 + g][d]
+                              : s_o[w][g][d] + s_o[w][8 + g][d];
+      Os += o * wt;
     }
     float *ws = p.ws + ((static_cast<int64_t>(b) * p.n_q_heads + kvh * G + g) * p.n_split + split) * (D + 2);
     ws[d] = Os;
@@ -776,7 +870,7 @@ __global__ __launch_bounds__(D) void decode_combine_kernel(const DecodeParams p)
 template <typename T, int D, int GT, bool kPaged>
 hipError_t launch_split(const DecodeParams &p, hipStream_t stream) {
   const dim3 grid(p.n_split, p.n_kv_heads, p.batch);
-  if constexpr (std::is_same_v<T, uint16_t> && PRCR_DEC_MFMA) {
+  if constexpr (std::is_same_v<T, uint16_t>) {
     if constexpr (kPaged) {
       if (p.block_size % 16 == 0)
         decode_partial_bf16_kernel<D, GT, true, true><<<grid, kWaves * kWave, 0, stream>>>(p);
@@ -796,8 +890,11 @@ hipError_t launch_split(const DecodeParams &p, hipStream_t stream) {
 
 template <typename T, int D, bool kPaged>
 hipError_t dispatch_group(const DecodeParams &p, int G, hipStream_t stream) {
-  if (G <= 1) return launch_split<T, D, 1, kPaged>(p, stream);
-  if (G <= 2) return launch_split<T, D, 2, kPaged>(p, stream);
+  // (The bf16 kernel's products have room for 4 or 8 heads at the same cost as fewer.)
+  if constexpr (!std::is_same_v<T, uint16_t>) {
+    if (G <= 1) return launch_split<T, D, 1, kPaged>(p, stream);
+    if (G <= 2) return launch_split<T, D, 2, kPaged>(p, stream);
+  }
   if (G <= 4) return launch_split<T, D, 4, kPaged>(p, stream);
   return launch_split<T, D, 8, kPaged>(p, stream);
 }
