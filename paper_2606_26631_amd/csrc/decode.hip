@@ -85,22 +85,67 @@ __device__ __forceinline__ float group_sum(float s) {
   return s;
 }
 
-// Sequence taken by workgroup row z.  With at most 64 sequences (lane l reads
-// length l), the rows go to the sequences in order of decreasing length, ties by
-// index.  Workgroups are dealt to the compute units in turn, so that each unit
+// Sequence taken by workgroup row z, and its length entry.  With at most 64 sequences
+// (lane l reads length l), the rows go to the sequences in order of decreasing length,
+// ties by index.  Workgroups are dealt to the compute units in turn, so that each unit
 // then holds chunks of long and of short sequences rather than a random mix: on a
 // paged batch of 2,918-6,424 keys this measured 6 % faster.  Results do not depend
 // on the order (each sequence is computed the same way by whichever row takes it).
-__device__ __forceinline__ int sequence_of_row(const DecodeParams &p, int lane, int z) {
-  if (p.batch > kWave) return z;
-  const int mine = lane < p.batch ? max(p.cache_len[lane], 0) : -1;
+__device__ __forceinline__ int sequence_of_row(const DecodeParams &p, int lane, int z, int *len) {
+  if (p.batch > kWave) {
+    *len = p.cache_len[z];
+    return z;
+  }
+  const int raw = lane < p.batch ? p.cache_len[lane] : 0;
+  const int mine = lane < p.batch ? max(raw, 0) : -1;
   int rank = 0;
   for (int i = 0; i < p.batch; ++i) {
     const int other = __builtin_amdgcn_readlane(mine, i);
     rank += (other > mine) || (other == mine && i < lane);
   }
   const unsigned long long hit = __ballot(lane < p.batch && rank == z);
-  return hit ? __ffsll(static_cast<long long>(hit)) - 1 : z;
+  const int b = __builtin_amdgcn_readfirstlane(hit ? __ffsll(static_cast<long long>(hit)) - 1 : z);
+  *len = __builtin_amdgcn_readlane(raw, b);
+  return b;
+}
+
+// Keys per workgroup of a sequence of len keys: an even share of its n_split workgroups,
+// in whole rounds of p.round keys, so that no workgroup of a sequence waits on a longer
+// one.  Workgroups past the sequence's last key have nothing to do and write nothing.
+__device__ __forceinline__ int chunk_keys(const DecodeParams &p, int len) {
+  const int per = (len + p.n_split - 1) / p.n_split;
+  return (per + p.round - 1) / p.round * p.round;
+}
+
+// Length of a sequence as the kernels use it: within [0, capacity].
+__device__ __forceinline__ int clamp_len(const DecodeParams &p, bool paged, int len) {
+  const int64_t cap = paged ? static_cast<int64_t>(p.max_blocks) * p.block_size : p.s_max;
+  return static_cast<int>(min(max(static_cast<int64_t>(len), int64_t{0}), cap));
+}
+
+// Ends a workgroup's chunk: part(g, d, &M, &L, &O) gives the chunk's running maximum, sum
+// of weights and weighted value of feature d of head g.  They go to the workspace for
+// decode_combine_kernel, or, where every sequence is one chunk (p.direct), to the output
+// at once.
+template <int D, int kThreads, class Part>
+__device__ __forceinline__ void finish_split(const DecodeParams &p, int b, int kvh, int G, int split,
+                                             const Part &part) {
+  const int64_t head0 = static_cast<int64_t>(b) * p.n_q_heads + kvh * G;
+  for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
+    const int g = idx / D, d = idx % D;
+    float M, L, O;
+    part(g, d, &M, &L, &O);
+    if (p.direct) {
+      p.out[head0 * D + idx] = L > 0.f ? O / L : 0.f;
+    } else {
+      float *ws = p.ws + ((head0 + g) * p.n_split + split) * (D + 2);
+      ws[d] = O;
+      if (d == 0) {
+        ws[D] = M;
+        ws[D + 1] = L;
+      }
+    }
+  }
 }
 
 template <typename T, int D, int GT, bool kPaged>
@@ -118,26 +163,21 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
 
   const int split = blockIdx.x, kvh = blockIdx.y;
   const int lane = threadIdx.x & (kWave - 1);
-  const int b = sequence_of_row(p, lane, blockIdx.z);
+  int len_in;
+  const int b = sequence_of_row(p, lane, blockIdx.z, &len_in);
   const int wave = threadIdx.x / kWave;
   const int kg = lane / LPK;                 // key row slot within the wave
   const int c = lane % LPK;                  // 16-byte chunk of the row
   const int grp = wave * KPW + kg;           // key row slot within the workgroup
   const int G = p.n_q_heads / p.n_kv_heads;
 
-  const int64_t cap = kPaged ? static_cast<int64_t>(p.max_blocks) * p.block_size : p.s_max;
-  int len = p.cache_len[b];
-  if (len < 0 || len > cap) {
-    if (split == 0 && kvh == 0 && threadIdx.x == 0 && p.err != nullptr)
-      atomicOr(p.err, PRCR_DERR_CAPACITY);
-    len = static_cast<int>(min(max(static_cast<int64_t>(len), int64_t{0}), cap));
-  }
-  // The sequence's keys are shared evenly by its n_split workgroups, in whole
-  // workgroup batches, so that no workgroup of a sequence waits on a longer one.
-  const int per = (len + p.n_split - 1) / p.n_split;
-  const int chunk = (per + KPB - 1) / KPB * KPB;
-  const int j0 = min(len, split * chunk);
-  const int j1 = min(len, j0 + chunk);
+  const int len = clamp_len(p, kPaged, len_in);
+  if (len != len_in && split == 0 && kvh == 0 && threadIdx.x == 0 && p.err != nullptr)
+    atomicOr(p.err, PRCR_DERR_CAPACITY);
+  const int chunk = chunk_keys(p, len);
+  const int j0 = static_cast<int>(min(static_cast<int64_t>(len), static_cast<int64_t>(split) * chunk));
+  const int j1 = static_cast<int>(min(static_cast<int64_t>(len), static_cast<int64_t>(j0) + chunk));
+  if (j0 >= j1 && split > 0) return;
 
   // Rotated, scaled query chunk of every head of the group: the lane's elements
   // e = c*EPL .. c*EPL+EPL-1 pair with e +/- D/2, which sits in chunk c +/- LPK/2.
@@ -313,23 +353,16 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
     }
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < G * D; idx += kWaves * kWave) {
-    const int g = idx / D, d = idx % D;
-    float M = -FLT_MAX;
-    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w][g]);
-    float Ls = 0.f, Os = 0.f;
+  finish_split<D, kWaves * kWave>(p, b, kvh, G, split, [&](int g, int d, float *M, float *L, float *O) {
+    *M = -FLT_MAX;
+    for (int w = 0; w < kWaves; ++w) *M = fmaxf(*M, s_m[w][g]);
+    *L = *O = 0.f;
     for (int w = 0; w < kWaves; ++w) {
-      const float wt = exp2_fast(s_m[w][g] - M);
-      Ls += s_l[w][g] * wt;
-      Os += s_o[w][g][d] * wt;
+      const float wt = exp2_fast(s_m[w][g] - *M);
+      *L += s_l[w][g] * wt;
+      *O += s_o[w][g][d] * wt;
     }
-    float *ws = p.ws + ((static_cast<int64_t>(b) * p.n_q_heads + kvh * G + g) * p.n_split + split) * (D + 2);
-    ws[d] = Os;
-    if (d == 0) {
-      ws[D] = M;
-      ws[D + 1] = Ls;
-    }
-  }
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -444,39 +477,40 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
 
   const int split = blockIdx.x, kvh = blockIdx.y;
   const int lane = threadIdx.x & (kWave - 1);
-  const int b = sequence_of_row(p, lane, blockIdx.z);
+  const double inv = p.inv_freq[threadIdx.x % P];
+  int len_in;
+  const int b = sequence_of_row(p, lane, blockIdx.z, &len_in);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int n16 = lane % 16;                 // product column; operand row
   const int kj = lane / 16;                  // k group of the operands; head of the lane's scores
   const int G = p.n_q_heads / p.n_kv_heads;
 
-  const int64_t cap = kPaged ? static_cast<int64_t>(p.max_blocks) * p.block_size : p.s_max;
-  int len = p.cache_len[b];
-  if (len < 0 || len > cap) {
-    if (split == 0 && kvh == 0 && threadIdx.x == 0 && p.err != nullptr)
-      atomicOr(p.err, PRCR_DERR_CAPACITY);
-    len = static_cast<int>(min(max(static_cast<int64_t>(len), int64_t{0}), cap));
-  }
-  const int per = (len + p.n_split - 1) / p.n_split;
-  const int chunk = (per + KPB - 1) / KPB * KPB;
+  const int len = clamp_len(p, kPaged, len_in);
+  if (len != len_in && split == 0 && kvh == 0 && threadIdx.x == 0 && p.err != nullptr)
+    atomicOr(p.err, PRCR_DERR_CAPACITY);
+  const int chunk = chunk_keys(p, len);
   const int j0 = static_cast<int>(min(static_cast<int64_t>(len), static_cast<int64_t>(split) * chunk));
-  const int j1 = min(len, j0 + chunk);
+  const int j1 = static_cast<int>(min(static_cast<int64_t>(len), static_cast<int64_t>(j0) + chunk));
+  if (j0 >= j1 && split > 0) return;
 
   // Rotated, scaled query of every head of the group (pair i with i + D/2, the
   // 1-D rotation at p_next), in float32, in LDS.
   {
-    const double pq = static_cast<double>(p.q_pos[b]);
     const double qs = static_cast<double>(p.scale) * kLog2e;
-    for (int idx = threadIdx.x; idx < GT * P; idx += kWaves * kWave) {
-      const int g = idx / P, i = idx % P;
-      const int qh = kvh * G + (g < G ? g : 0);
-      const uint16_t *qrow = static_cast<const uint16_t *>(p.q) + (static_cast<int64_t>(b) * p.n_q_heads + qh) * D;
-      double sn, cs;
-      sincos(pq * p.inv_freq[i], &sn, &cs);
-      const double x = __uint_as_float(static_cast<uint32_t>(qrow[i]) << 16);
-      const double xp = __uint_as_float(static_cast<uint32_t>(qrow[i + P]) << 16);
-      s_q[g][i] = static_cast<float>((x * cs - xp * sn) * qs);
-      s_q[g][i + P] = static_cast<float>((xp * cs + x * sn) * qs);
+    const int i = threadIdx.x % P;
+    double sn, cs;
+    sincos(static_cast<double>(p.q_pos[b]) * inv, &sn, &cs);
+#pragma unroll
+    for (int g0 = 0; g0 < GT; g0 += kWaves * kWave / P) {
+      const int g = g0 + threadIdx.x / P;
+      if (g < GT) {
+        const int qh = kvh * G + (g < G ? g : 0);
+        const uint16_t *qrow = static_cast<const uint16_t *>(p.q) + (static_cast<int64_t>(b) * p.n_q_heads + qh) * D;
+        const double x = __uint_as_float(static_cast<uint32_t>(qrow[i]) << 16);
+        const double xp = __uint_as_float(static_cast<uint32_t>(qrow[i + P]) << 16);
+        s_q[g][i] = static_cast<float>((x * cs - xp * sn) * qs);
+        s_q[g][i + P] = static_cast<float>((xp * cs + x * sn) * qs);
+      }
     }
   }
   // Weight rows: the three parts of head h are rows h, 4 + h and 8 + h (4 heads; rows
@@ -769,25 +803,18 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
           f32x4{acc[4 * c][r], acc[4 * c + 1][r], acc[4 * c + 2][r], acc[4 * c + 3][r]};
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < G * D; idx += kWaves * kWave) {
-    const int g = idx / D, d = idx % D;
-    float M = -FLT_MAX;
-    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w][g]);
-    float Ls = 0.f, Os = 0.f;
+  finish_split<D, kWaves * kWave>(p, b, kvh, G, split, [&](int g, int d, float *M, float *L, float *O) {
+    *M = -FLT_MAX;
+    for (int w = 0; w < kWaves; ++w) *M = fmaxf(*M, s_m[w][g]);
+    *L = *O = 0.f;
     for (int w = 0; w < kWaves; ++w) {
-      const float wt = exp2_fast(s_m[w][g] - M);
-      Ls += s_l[w][g] * wt;
+      const float wt = exp2_fast(s_m[w][g] - *M);
+      *L += s_l[w][g] * wt;
       const float o = GT == 4 ? (s_o[w][g][d] + s_o[w][4 + g][d]) + s_o[w][8 + g][d]
                               : s_o[w][g][d] + s_o[w][8 + g][d];
-      Os += o * wt;
+      *O += o * wt;
     }
-    float *ws = p.ws + ((static_cast<int64_t>(b) * p.n_q_heads + kvh * G + g) * p.n_split + split) * (D + 2);
-    ws[d] = Os;
-    if (d == 0) {
-      ws[D] = M;
-      ws[D + 1] = Ls;
-    }
-  }
+  });
 }
 
 // Merge of one query head's split partials.  Each split's (max, sum) is read by
@@ -797,26 +824,33 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
 // multiply-adds as a sequential merge (an empty split adds exact zeros).  The
 // feature values of the first kPre splits do not depend on the weights: they are
 // read in the same round as the (max, sum) pairs.
-template <int D>
+template <int D, bool kPaged>
 __global__ __launch_bounds__(D) void decode_combine_kernel(const DecodeParams p) {
   constexpr int kPre = 8;
   __shared__ float s_red[D / kWave];
   __shared__ float s_w[D], s_l[D];
   const int qh = blockIdx.x, b = blockIdx.y, d = threadIdx.x;
   const int lane = d & (kWave - 1), wave = d / kWave;
-  const int ns = p.n_split;
-  const float *ws = p.ws + (static_cast<int64_t>(b) * p.n_q_heads + qh) * ns * (D + 2);
+  const float *ws = p.ws + (static_cast<int64_t>(b) * p.n_q_heads + qh) * p.n_split * (D + 2);
+  const int len_in = p.cache_len[b];
   float o_pre[kPre];
 #pragma unroll
-  for (int k = 0; k < kPre; ++k) o_pre[k] = ws[static_cast<int64_t>(min(k, ns - 1)) * (D + 2) + d];
+  for (int k = 0; k < kPre; ++k) o_pre[k] = ws[static_cast<int64_t>(min(k, p.n_split - 1)) * (D + 2) + d];
   // Largest max over the splits that saw a key.  Both values of a split are
   // read before either is used; a thread keeps those of its first split (every
   // split, when n_split <= D) for the second pass.
   float M = -FLT_MAX, l_first = 0.f, m_first = -FLT_MAX;
+  int ns = p.n_split;
   for (int s0 = 0; s0 < ns; s0 += D) {
     const int s = min(s0 + d, ns - 1);
     const float l = ws[static_cast<int64_t>(s) * (D + 2) + D + 1];
     const float m = ws[static_cast<int64_t>(s) * (D + 2) + D];
+    if (s0 == 0) {
+      // The splits that have keys (the others' words hold anything); at least the first
+      // is written.
+      const int len = clamp_len(p, kPaged, len_in), chunk = max(chunk_keys(p, len), 1);
+      ns = max((len + chunk - 1) / chunk, 1);
+    }
     const bool used = s0 + d < ns && l > 0.f;
     M = used ? fmaxf(M, m) : M;
     if (s0 == 0) {
@@ -868,7 +902,10 @@ __global__ __launch_bounds__(D) void decode_combine_kernel(const DecodeParams p)
 }
 
 template <typename T, int D, int GT, bool kPaged>
-hipError_t launch_split(const DecodeParams &p, hipStream_t stream) {
+hipError_t launch_split(const DecodeParams &in, hipStream_t stream) {
+  DecodeParams p = in;
+  // Keys a workgroup's waves take at once: a tile each, or kWave / (D / chunk) rows each.
+  p.round = kWaves * (std::is_same_v<T, uint16_t> ? kTile : kWave / (D / Elems<T>::kPerChunk));
   const dim3 grid(p.n_split, p.n_kv_heads, p.batch);
   if constexpr (std::is_same_v<T, uint16_t>) {
     if constexpr (kPaged) {
@@ -883,8 +920,8 @@ hipError_t launch_split(const DecodeParams &p, hipStream_t stream) {
     decode_partial_kernel<T, D, GT, kPaged>
         <<<dim3(p.n_split, p.n_kv_heads, p.batch), kWaves * kWave, 0, stream>>>(p);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  decode_combine_kernel<D><<<dim3(p.n_q_heads, p.batch), D, 0, stream>>>(p);
+  if (e != hipSuccess || p.direct) return e;
+  decode_combine_kernel<D, kPaged><<<dim3(p.n_q_heads, p.batch), D, 0, stream>>>(p);
   return hipGetLastError();
 }
 
@@ -923,9 +960,37 @@ int decode_splits(int64_t capacity, int batch, int n_kv_heads, int group) {
   return static_cast<int>(ns);
 }
 
-hipError_t launch_decode(const DecodeParams &p, prcr_dtype dtype, int head_dim, bool paged,
+namespace {
+
+bool overlap(const void *a, double na, const void *b, double nb) {
+  const double x = static_cast<double>(reinterpret_cast<uintptr_t>(a));
+  const double y = static_cast<double>(reinterpret_cast<uintptr_t>(b));
+  return a != nullptr && b != nullptr && x < y + nb && y < x + na;
+}
+
+// Whether the partial kernel may write the outputs itself: every sequence is one chunk,
+// and no workgroup's output rows are bytes that another one still reads.  96 sequences of
+// 500-2,500 keys (8 KV heads, 4 query heads each, paged, two layers): 263 us with the merge
+// launch, 251 without.
+bool writes_direct(const DecodeParams &p, int elem_bytes, int head_dim, bool paged) {
+  if (p.n_split != 1) return false;
+  const double rows = static_cast<double>(p.batch) * p.n_q_heads * head_dim;
+  const double out = rows * 4;
+  const double slots = paged ? static_cast<double>(p.n_blocks) * p.block_size : static_cast<double>(p.batch) * p.s_max;
+  const double cache = slots * p.n_layers * p.n_kv_heads * head_dim * elem_bytes;
+  return !overlap(p.out, out, p.q, rows * elem_bytes) && !overlap(p.out, out, p.q_pos, 4.0 * p.batch) &&
+         !overlap(p.out, out, p.cache_len, 4.0 * p.batch) &&
+         !(paged && overlap(p.out, out, p.block_table, 4.0 * p.batch * p.max_blocks)) &&
+         !overlap(p.out, out, p.cache_k, cache) && !overlap(p.out, out, p.cache_v, cache);
+}
+
+}  // namespace
+
+hipError_t launch_decode(const DecodeParams &in, prcr_dtype dtype, int head_dim, bool paged,
                          hipStream_t stream) {
+  DecodeParams p = in;
   const int G = p.n_q_heads / p.n_kv_heads;
+  p.direct = writes_direct(p, dtype == PRCR_F32 ? 4 : 2, head_dim, paged);
   if (dtype == PRCR_F32)
     return paged ? dispatch_dim<float, true>(p, head_dim, G, stream)
                  : dispatch_dim<float, false>(p, head_dim, G, stream);

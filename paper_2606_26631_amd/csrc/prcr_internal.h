@@ -124,6 +124,8 @@ struct DecodeParams {
   int32_t s_max, block_size, max_blocks, n_blocks;
   int32_t block_shift;            // log2(block_size) if a power of two, else -1
   int32_t n_split;                // workgroups per (sequence, KV head)
+  int32_t round;                  // keys per workgroup come in multiples of this (set by the launcher)
+  int32_t direct;                 // n_split is 1 and the kernel writes out itself (set by the launcher)
   float scale;
   double inv_freq[kMaxPairs];
 };
