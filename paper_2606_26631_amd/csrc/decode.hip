@@ -756,9 +756,10 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
         pa[kPT - 1] = *reinterpret_cast<const u32x4 *>(&s_p[wave][16 + n16 % 8][4 * kj]);
         const u16x2 most = __builtin_bit_cast(u16x2, n16 < 8 ? 0xFFFFFFFFu : 0x00800080u);
 #pragma unroll
-        for (int w = 0; w < 4; ++w)
-          pa[kPT - 1][w] = __builtin_bit_cast(
-              uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, pa[kPT - 1][w]), most));
+        for (int w = 0; w < 4; ++w) {
+          const uint32_t two = pa[kPT - 1][w];   // (a bit cast of the element itself takes element 0)
+          pa[kPT - 1][w] = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, two), most));
+        }
       }
       // A zero weight times a value read from another row could make a NaN: values
       // of keys without weight are taken as zero.
