@@ -838,88 +838,114 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
   });
 }
 
-// Merge of one query head's split partials.  Each split's (max, sum) is read by
-// one thread, D splits at a time, so that the reads go out together instead of
-// one after another's use; the weights pass through LDS, and every thread then
-// accumulates its feature over the splits in split order with the same fused
-// multiply-adds as a sequential merge (an empty split adds exact zeros).  The
-// feature values of the first kPre splits do not depend on the weights: they are
-// read in the same round as the (max, sum) pairs.
-template <int D, bool kPaged>
-__global__ __launch_bounds__(D) void decode_combine_kernel(const DecodeParams p) {
-  constexpr int kPre = 8;
-  __shared__ float s_red[D / kWave];
-  __shared__ float s_w[D], s_l[D];
-  const int qh = blockIdx.x, b = blockIdx.y, d = threadIdx.x;
-  const int lane = d & (kWave - 1), wave = d / kWave;
-  const float *ws = p.ws + (static_cast<int64_t>(b) * p.n_q_heads + qh) * p.n_split * (D + 2);
+// Over the wave's four rows of 16 lanes (the same value in every lane): register lane
+// permutations and reads, where a shuffle is a round trip through the LDS unit per step.
+__device__ __forceinline__ float lane_value(float x, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+__device__ __forceinline__ float wave_max(float x) {
+  x = row_max16(x);
+  return fmaxf(fmaxf(lane_value(x, 0), lane_value(x, 16)), fmaxf(lane_value(x, 32), lane_value(x, 48)));
+}
+__device__ __forceinline__ float wave_sum(float x) {
+  x = group_sum<16>(x);
+  return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
+}
+
+// Merge of one query head's split partials, by kHeadWaves waves (each takes every
+// kHeadWaves-th split).  What it costs is one launch and its dependent rounds of loads, so
+// everything the first kPre splits need goes out in one round: the length (which gives
+// the number of splits that have keys; the others' words hold anything), the (max, sum)
+// pairs, one split per lane, and the features, which do not depend on the weights.  With
+// up to kPre splits a wave needs neither a second round nor a barrier; with more, four
+// waves share a head and meet once in LDS.  Against one thread per feature, with the
+// weights through LDS, a layer took 22.7 us and takes 19.7 (one sequence of 16,000 keys, 8
+// KV heads of 8 query heads, 64 splits), 14.0 and 13.1 (four of 1,500-3,000 keys, 4 KV
+// heads of 7, 32 splits), and the same with 3 splits, where launch and one round are all.
+constexpr int kPre = 8;
+template <int D, bool kPaged, int kHeadWaves>
+__global__ __launch_bounds__(kWaves * kWave) void decode_combine_kernel(const DecodeParams p) {
+  constexpr int F = D / kWave;               // features per lane: lane + 64 f
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int part = wave % kHeadWaves;        // this wave's splits: part, part + kHeadWaves, ...
+  const int64_t heads = static_cast<int64_t>(p.batch) * p.n_q_heads;
+  const int64_t head = static_cast<int64_t>(blockIdx.x) * (kWaves / kHeadWaves) + wave / kHeadWaves;
+  if (head >= heads) return;                 // (whole workgroups only where waves share a head)
+  const int b = static_cast<int>(head / p.n_q_heads);
+  const float *ws = p.ws + head * p.n_split * (D + 2);
+  auto split_row = [&](int i) -> const float * {   // the wave's i-th split (clamped: always in the array)
+    return ws + static_cast<int64_t>(min(i * kHeadWaves + part, p.n_split - 1)) * (D + 2);
+  };
   const int len_in = p.cache_len[b];
-  float o_pre[kPre];
+  float m = split_row(lane)[D], l = split_row(lane)[D + 1];
+  float o[kPre][F];
 #pragma unroll
-  for (int k = 0; k < kPre; ++k) o_pre[k] = ws[static_cast<int64_t>(min(k, p.n_split - 1)) * (D + 2) + d];
-  // Largest max over the splits that saw a key.  Both values of a split are
-  // read before either is used; a thread keeps those of its first split (every
-  // split, when n_split <= D) for the second pass.
-  float M = -FLT_MAX, l_first = 0.f, m_first = -FLT_MAX;
-  int ns = p.n_split;
-  for (int s0 = 0; s0 < ns; s0 += D) {
-    const int s = min(s0 + d, ns - 1);
-    const float l = ws[static_cast<int64_t>(s) * (D + 2) + D + 1];
-    const float m = ws[static_cast<int64_t>(s) * (D + 2) + D];
-    if (s0 == 0) {
-      // The splits that have keys (the others' words hold anything); at least the first
-      // is written.
-      const int len = clamp_len(p, kPaged, len_in), chunk = max(chunk_keys(p, len), 1);
-      ns = max((len + chunk - 1) / chunk, 1);
-    }
-    const bool used = s0 + d < ns && l > 0.f;
-    M = used ? fmaxf(M, m) : M;
-    if (s0 == 0) {
-      l_first = used ? l : 0.f;
-      m_first = m;
-    }
-  }
-  for (int o = kWave / 2; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-  if (lane == 0) s_red[wave] = M;
-  __syncthreads();
-  M = s_red[0];
+  for (int k = 0; k < kPre; ++k)
 #pragma unroll
-  for (int w = 1; w < D / kWave; ++w) M = fmaxf(M, s_red[w]);
-  float Ls = 0.f, Os = 0.f;
-  for (int s0 = 0; s0 < ns; s0 += D) {
-    const int s = s0 + d;
-    float l = l_first, m = m_first;
-    if (s0 > 0) {
-      const int sc = min(s, ns - 1);
-      l = ws[static_cast<int64_t>(sc) * (D + 2) + D + 1];
-      m = ws[static_cast<int64_t>(sc) * (D + 2) + D];
-      l = s < ns && l > 0.f ? l : 0.f;
+    for (int f = 0; f < F; ++f) o[k][f] = split_row(k)[lane + kWave * f];
+
+  const int len = clamp_len(p, kPaged, len_in), chunk = max(chunk_keys(p, len), 1);
+  const int used = max((len + chunk - 1) / chunk, 1);   // (an empty sequence writes one empty split)
+  const int cnt = (used - part + kHeadWaves - 1) / kHeadWaves;
+  float M = -FLT_MAX, L = 0.f, O[F];
+#pragma unroll
+  for (int f = 0; f < F; ++f) O[f] = 0.f;
+  for (int i0 = 0; i0 < cnt; i0 += kWave) {
+    if (i0 > 0) {
+      m = split_row(i0 + lane)[D];
+      l = split_row(i0 + lane)[D + 1];
     }
-    const float w = l > 0.f ? exp2_fast(m - M) : 0.f;
-    __syncthreads();
-    s_w[d] = w;
-    s_l[d] = l;
-    __syncthreads();
-    const int cnt = min(D, ns - s0);
-    const float *o = ws + static_cast<int64_t>(s0) * (D + 2) + d;
-    int k0 = 0;
-    if (s0 == 0) {
+    const bool valid = i0 + lane < cnt && l > 0.f;
+    float mx = valid ? m : -FLT_MAX;
+    mx = fmaxf(M, wave_max(mx));
+    const float corr = exp2_fast(M - mx);
+    M = mx;
+    const float w = valid ? exp2_fast(m - M) : 0.f;
+    L = fmaf(L, corr, wave_sum(valid ? l * w : 0.f));
+#pragma unroll
+    for (int f = 0; f < F; ++f) O[f] *= corr;
+    const int n = min(kWave, cnt - i0);
+    for (int k0 = 0; k0 < n; k0 += kPre) {
+      if (i0 + k0 > 0) {
+#pragma unroll
+        for (int k = 0; k < kPre; ++k)
+#pragma unroll
+          for (int f = 0; f < F; ++f) o[k][f] = split_row(i0 + k0 + k)[lane + kWave * f];
+      }
 #pragma unroll
       for (int k = 0; k < kPre; ++k) {
-        if (k < cnt) {
-          Ls = fmaf(s_l[k], s_w[k], Ls);
-          Os = fmaf(o_pre[k], s_w[k], Os);
-        }
+        if (k0 + k >= n) break;
+        const float wk = lane_value(w, k0 + k);
+#pragma unroll
+        for (int f = 0; f < F; ++f) O[f] = fmaf(o[k][f], wk, O[f]);
       }
-      k0 = kPre;
-    }
-#pragma unroll 4
-    for (int k = k0; k < cnt; ++k) {
-      Ls = fmaf(s_l[k], s_w[k], Ls);
-      Os = fmaf(o[static_cast<int64_t>(k) * (D + 2)], s_w[k], Os);
     }
   }
-  p.out[(static_cast<int64_t>(b) * p.n_q_heads + qh) * D + d] = Ls > 0.f ? Os / Ls : 0.f;
+  if constexpr (kHeadWaves > 1) {
+    static_assert(kHeadWaves == kWaves, "a workgroup's waves share one head");
+    __shared__ float s_m[kWaves], s_l[kWaves], s_o[kWaves][D];
+    if (lane == 0) {
+      s_m[wave] = M;
+      s_l[wave] = L;
+    }
+#pragma unroll
+    for (int f = 0; f < F; ++f) s_o[wave][lane + kWave * f] = O[f];
+    __syncthreads();
+    if (threadIdx.x >= D) return;
+    M = -FLT_MAX;
+    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w]);
+    float Ls = 0.f, Os = 0.f;
+    for (int w = 0; w < kWaves; ++w) {
+      const float wt = exp2_fast(s_m[w] - M);
+      Ls = fmaf(s_l[w], wt, Ls);
+      Os = fmaf(s_o[w][threadIdx.x], wt, Os);
+    }
+    p.out[head * D + threadIdx.x] = Ls > 0.f ? Os / Ls : 0.f;
+  } else {
+#pragma unroll
+    for (int f = 0; f < F; ++f) p.out[head * D + lane + kWave * f] = L > 0.f ? O[f] / L : 0.f;
+  }
 }
 
 template <typename T, int D, int GT, bool kPaged>
@@ -942,7 +968,11 @@ hipError_t launch_split(const DecodeParams &in, hipStream_t stream) {
         <<<dim3(p.n_split, p.n_kv_heads, p.batch), kWaves * kWave, 0, stream>>>(p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.direct) return e;
-  decode_combine_kernel<D, kPaged><<<dim3(p.n_q_heads, p.batch), D, 0, stream>>>(p);
+  const int64_t heads = static_cast<int64_t>(p.batch) * p.n_q_heads;
+  if (p.n_split <= kPre)
+    decode_combine_kernel<D, kPaged, 1><<<static_cast<unsigned>((heads + kWaves - 1) / kWaves), kWaves * kWave, 0, stream>>>(p);
+  else
+    decode_combine_kernel<D, kPaged, kWaves><<<static_cast<unsigned>(heads), kWaves * kWave, 0, stream>>>(p);
   return hipGetLastError();
 }
 
