@@ -2,7 +2,8 @@
 
 Every source is compiled with hipcc for gfx950 only; the library is linked into
 the package directory so that the Python binding, the tests and the benchmark
-load it from the source tree.
+load it from the source tree.  The binding's native module (host code, against the
+installed torch and Python) is built beside it.
 """
 from __future__ import annotations
 
@@ -11,6 +12,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -25,6 +27,10 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 COPYREF_SOURCES = ["copyref.hip"]
 COPYREF_OUT = os.path.join(PKG, "libprcr_copyref.so")
 SOURCES = ["api.cpp", "axis_map.cpp", "decode.hip", "decode_static.hip", "prefill.hip", "reassign.hip", "rebind.hip", "store_raw.hip"]
+
+# The binding's native module: C++ against torch's and Python's headers.
+NATIVE_SOURCE = "native_calls.cpp"
+NATIVE_OUT = os.path.join(PKG, "_prcr_native.so")
 
 # Packed-FP32 instructions are disabled for all device code; the host pass of
 # hipcc warns that it does not know the feature, which is harmless.
@@ -65,14 +71,49 @@ def _link(objs, out: str, verbose: bool) -> None:
     os.replace(tmp, out)
 
 
+def _compile_native(verbose: bool) -> str:
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    obj = os.path.join(BUILD_DIR, os.path.splitext(NATIVE_SOURCE)[0] + ".o")
+    rocm = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(hipcc()))), "include")
+    incs = [*include_paths(), sysconfig.get_paths()["include"], rocm]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-Wall", "-fvisibility=hidden",
+           "-D__HIP_PLATFORM_AMD__", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-I{INCLUDE}", *[a for i in incs for a in ("-isystem", i)],
+           "-c", os.path.join(CSRC, NATIVE_SOURCE), "-o", obj]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"the host compiler failed for {NATIVE_SOURCE}:\n{r.stdout}\n{r.stderr}")
+    return obj
+
+
+def _link_native(obj: str, verbose: bool) -> None:
+    from torch.utils.cpp_extension import library_paths
+    tmp = NATIVE_OUT + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-shared", obj, "-o", tmp, *[f"-L{d}" for d in library_paths()],
+           "-ltorch_python", "-ltorch_cpu", "-lc10", f"-L{PKG}", f"-l:{os.path.basename(OUT)}",
+           "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, NATIVE_OUT)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source for gfx950 and link libprcr.so, and the measurement's
-    reference copy kernels into libprcr_copyref.so; returns libprcr.so's path."""
+    """Compile every source for gfx950 and link libprcr.so, the measurement's reference
+    copy kernels into libprcr_copyref.so, and the binding's native module; returns
+    libprcr.so's path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + len(COPYREF_SOURCES))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + len(COPYREF_SOURCES) + 1)) as ex:
+        native = ex.submit(_compile_native, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES + COPYREF_SOURCES))
     _link(objs[:len(SOURCES)], OUT, verbose)
     _link(objs[len(SOURCES):], COPYREF_OUT, verbose)
+    _link_native(native.result(), verbose)
     return OUT
 
 
