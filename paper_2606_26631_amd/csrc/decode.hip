@@ -85,23 +85,54 @@ __device__ __forceinline__ float group_sum(float s) {
   return s;
 }
 
+// Workgroup barrier that orders LDS accesses only: loads from memory stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Sequence taken by workgroup row z, and its length entry.  With at most 64 sequences
 // (lane l reads length l), the rows go to the sequences in order of decreasing length,
 // ties by index.  Workgroups are dealt to the compute units in turn, so that each unit
 // then holds chunks of long and of short sequences rather than a random mix: on a
 // paged batch of 2,918-6,424 keys this measured 6 % faster.  Results do not depend
 // on the order (each sequence is computed the same way by whichever row takes it).
+//
+// Every workgroup does this before its first key, so its waves share the work: a lane's
+// rank is the number of keys (length, then lower index) above its own, and wave w counts
+// among sequences 16 w to 16 w + 15.  With 64 sequences every wave counting all of them
+// took 2.7 us (two compares each) or 1.1 us (one); the shared count takes 0.6.
 __device__ __forceinline__ int sequence_of_row(const DecodeParams &p, int lane, int z, int *len) {
   if (p.batch > kWave) {
     *len = p.cache_len[z];
     return z;
   }
+  constexpr int kShare = kWave / kWaves;     // sequences a wave counts
   const int raw = lane < p.batch ? p.cache_len[lane] : 0;
-  const int mine = lane < p.batch ? max(raw, 0) : -1;
+  if (p.batch == 1) {
+    *len = __builtin_amdgcn_readfirstlane(raw);
+    return 0;
+  }
+  // Order of the lengths as one number: those above 2^25 - 1 count as equal.
+  const uint32_t mine = lane < p.batch ? (static_cast<uint32_t>(min(max(raw, 0), (1 << 25) - 1)) << 6 | (63 - lane)) + 1 : 0;
+  auto above = [&](int i0, int n) -> int {
+    int count = 0;
+#pragma unroll
+    for (int i = 0; i < n; ++i)
+      count += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(mine), i0 + i)) > mine ? 1 : 0;
+    return count;
+  };
   int rank = 0;
-  for (int i = 0; i < p.batch; ++i) {
-    const int other = __builtin_amdgcn_readlane(mine, i);
-    rank += (other > mine) || (other == mine && i < lane);
+  if (p.batch <= kShare) {
+    for (int i0 = 0; i0 < p.batch; i0 += 4) rank += above(i0, 4);
+  } else {
+    __shared__ int s_rank[kWaves][kWave];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    s_rank[wave][lane] = above(wave * kShare, kShare);
+    lds_barrier();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) rank += s_rank[w][lane];
   }
   const unsigned long long hit = __ballot(lane < p.batch && rank == z);
   const int b = __builtin_amdgcn_readfirstlane(hit ? __ffsll(static_cast<long long>(hit)) - 1 : z);
@@ -114,7 +145,7 @@ __device__ __forceinline__ int sequence_of_row(const DecodeParams &p, int lane, 
 // one.  Workgroups past the sequence's last key have nothing to do and write nothing.
 __device__ __forceinline__ int chunk_keys(const DecodeParams &p, int len) {
   const int per = (len + p.n_split - 1) / p.n_split;
-  return (per + p.round - 1) / p.round * p.round;
+  return (per + p.round - 1) & -p.round;   // (a power of two)
 }
 
 // Length of a sequence as the kernels use it: within [0, capacity].
@@ -123,23 +154,53 @@ __device__ __forceinline__ int clamp_len(const DecodeParams &p, bool paged, int 
   return static_cast<int>(min(max(static_cast<int64_t>(len), int64_t{0}), cap));
 }
 
-// Ends a workgroup's chunk: part(g, d, &M, &L, &O) gives the chunk's running maximum, sum
-// of weights and weighted value of feature d of head g.  They go to the workspace for
-// decode_combine_kernel, or, where every sequence is one chunk (p.direct), to the output
-// at once.
-template <int D, int kThreads, class Part>
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // at any float
+
+// Ends a workgroup's chunk: merges its waves' running maxima, sums of weights and weighted
+// values (a head's value is the sum of kParts rows, kStep rows apart) and writes them to the
+// workspace for decode_combine_kernel, or, where every sequence is one chunk (p.direct), to
+// the output at once.  Four features of one head per thread, every LDS read issued before
+// the first use; a feature at a time this took 0.6 us of the 4 us that a short chunk takes.
+template <int D, int GT, int kParts, int kStep, int kRows>
 __device__ __forceinline__ void finish_split(const DecodeParams &p, int b, int kvh, int G, int split,
-                                             const Part &part) {
+                                             const float (&s_m)[kWaves][GT], const float (&s_l)[kWaves][GT],
+                                             const float (&s_o)[kWaves][kRows][D]) {
   const int64_t head0 = static_cast<int64_t>(b) * p.n_q_heads + kvh * G;
-  for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
-    const int g = idx / D, d = idx % D;
-    float M, L, O;
-    part(g, d, &M, &L, &O);
+#pragma unroll
+  for (int u = 0; u < (GT * D / 4 + kWaves * kWave - 1) / (kWaves * kWave); ++u) {
+    const int idx = u * kWaves * kWave + threadIdx.x;
+    const int g = idx / (D / 4), d = idx % (D / 4) * 4;
+    if (g >= G) break;
+    float m[kWaves], l[kWaves];
+    f32x4 o[kWaves][kParts];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      m[w] = s_m[w][g];
+      l[w] = s_l[w][g];
+#pragma unroll
+      for (int q = 0; q < kParts; ++q) o[w][q] = *reinterpret_cast<const f32x4 *>(&s_o[w][q * kStep + g][d]);
+    }
+    float M = -FLT_MAX, L = 0.f;
+    f32x4 O = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, m[w]);
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float wt = exp2_fast(m[w] - M);
+      L += l[w] * wt;
+      f32x4 v = o[w][0];
+#pragma unroll
+      for (int q = 1; q < kParts; ++q) v += o[w][q];
+      O += v * wt;
+    }
     if (p.direct) {
-      p.out[head0 * D + idx] = L > 0.f ? O / L : 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) O[e] = L > 0.f ? O[e] / L : 0.f;
+      *reinterpret_cast<f32x4_any *>(p.out + (head0 + g) * D + d) = O;
     } else {
       float *ws = p.ws + ((head0 + g) * p.n_split + split) * (D + 2);
-      ws[d] = O;
+      *reinterpret_cast<f32x4_any *>(ws + d) = O;
       if (d == 0) {
         ws[D] = M;
         ws[D + 1] = L;
@@ -159,7 +220,7 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
   static_assert(LPK >= 2 && kWave % LPK == 0, "unsupported head_dim");
   __shared__ float s_m[kWaves][GT];
   __shared__ float s_l[kWaves][GT];
-  __shared__ float s_o[kWaves][GT][D];
+  __shared__ __align__(16) float s_o[kWaves][GT][D];
 
   const int split = blockIdx.x, kvh = blockIdx.y;
   const int lane = threadIdx.x & (kWave - 1);
@@ -353,16 +414,7 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
     }
   }
   __syncthreads();
-  finish_split<D, kWaves * kWave>(p, b, kvh, G, split, [&](int g, int d, float *M, float *L, float *O) {
-    *M = -FLT_MAX;
-    for (int w = 0; w < kWaves; ++w) *M = fmaxf(*M, s_m[w][g]);
-    *L = *O = 0.f;
-    for (int w = 0; w < kWaves; ++w) {
-      const float wt = exp2_fast(s_m[w][g] - *M);
-      *L += s_l[w][g] * wt;
-      *O += s_o[w][g][d] * wt;
-    }
-  });
+  finish_split<D, GT, 1, 1>(p, b, kvh, G, split, s_m, s_l, s_o);
 }
 
 // ---------------------------------------------------------------------------
@@ -389,7 +441,6 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
 // of 2,756-4,256 keys, 8 KV heads and 4 query heads each 81.7, now 79.7 (458 MB).
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ f32x4 mfma_16x16x32(u32x4 a, u32x4 b, f32x4 c) {
@@ -403,13 +454,6 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Workgroup barrier that orders LDS accesses only: loads from memory stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Part `part` (0, 1, 2) of the three-way bf16 split of x, as bf16 bits in the
@@ -824,18 +868,7 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
           f32x4{acc[4 * c][r], acc[4 * c + 1][r], acc[4 * c + 2][r], acc[4 * c + 3][r]};
   }
   __syncthreads();
-  finish_split<D, kWaves * kWave>(p, b, kvh, G, split, [&](int g, int d, float *M, float *L, float *O) {
-    *M = -FLT_MAX;
-    for (int w = 0; w < kWaves; ++w) *M = fmaxf(*M, s_m[w][g]);
-    *L = *O = 0.f;
-    for (int w = 0; w < kWaves; ++w) {
-      const float wt = exp2_fast(s_m[w][g] - *M);
-      *L += s_l[w][g] * wt;
-      const float o = GT == 4 ? (s_o[w][g][d] + s_o[w][4 + g][d]) + s_o[w][8 + g][d]
-                              : s_o[w][g][d] + s_o[w][8 + g][d];
-      *O += o * wt;
-    }
-  });
+  finish_split<D, GT, GT == 4 ? 3 : 2, GT>(p, b, kvh, G, split, s_m, s_l, s_o);
 }
 
 // Over the wave's four rows of 16 lanes (the same value in every lane): register lane
@@ -855,22 +888,27 @@ __device__ __forceinline__ float wave_sum(float x) {
 // Merge of one query head's split partials, by kHeadWaves waves (each takes every
 // kHeadWaves-th split).  What it costs is one launch and its dependent rounds of loads, so
 // everything the first kPre splits need goes out in one round: the length (which gives
-// the number of splits that have keys; the others' words hold anything), the (max, sum)
-// pairs, one split per lane, and the features, which do not depend on the weights.  With
-// up to kPre splits a wave needs neither a second round nor a barrier; with more, four
-// waves share a head and meet once in LDS.  Against one thread per feature, with the
-// weights through LDS, a layer took 22.7 us and takes 19.7 (one sequence of 16,000 keys, 8
-// KV heads of 8 query heads, 64 splits), 14.0 and 13.1 (four of 1,500-3,000 keys, 4 KV
-// heads of 7, 32 splits), and the same with 3 splits, where launch and one round are all.
+// the splits that have keys; the others' words hold anything), the (max, sum) pairs, one
+// split per lane, and the features, which do not depend on the weights.  With up to kPre
+// splits a wave needs neither a second round nor a barrier; with more, 4 or 16 waves share
+// a head and meet once in LDS: 16 where 4 would need more than two rounds (125 splits of
+// one sequence of 16,000 keys: 3.4 us with 4 waves, 3.0 with 16).  Against one thread per
+// feature, with the weights through LDS, a layer took 22.7 us and takes 19.7 (one sequence
+// of 16,000 keys, 8 KV heads of 8 query heads, 64 splits), 14.0 and 13.1 (four of
+// 1,500-3,000 keys, 4 KV heads of 7, 32 splits), and the same with 3 splits, where launch
+// and one round are all.
 constexpr int kPre = 8;
 template <int D, bool kPaged, int kHeadWaves>
-__global__ __launch_bounds__(kWaves * kWave) void decode_combine_kernel(const DecodeParams p) {
-  constexpr int F = D / kWave;               // features per lane: lane + 64 f
+__global__ __launch_bounds__((kHeadWaves > kWaves ? kHeadWaves : kWaves) * kWave) void decode_combine_kernel(
+    const DecodeParams p) {
+  constexpr int F = D / kWave;               // features per lane: F * lane + f
+  constexpr int kBlockWaves = kHeadWaves > kWaves ? kHeadWaves : kWaves;
+  typedef float feat __attribute__((ext_vector_type(F), aligned(4)));
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int part = wave % kHeadWaves;        // this wave's splits: part, part + kHeadWaves, ...
   const int64_t heads = static_cast<int64_t>(p.batch) * p.n_q_heads;
-  const int64_t head = static_cast<int64_t>(blockIdx.x) * (kWaves / kHeadWaves) + wave / kHeadWaves;
+  const int64_t head = static_cast<int64_t>(blockIdx.x) * (kBlockWaves / kHeadWaves) + wave / kHeadWaves;
   if (head >= heads) return;                 // (whole workgroups only where waves share a head)
   const int b = static_cast<int>(head / p.n_q_heads);
   const float *ws = p.ws + head * p.n_split * (D + 2);
@@ -879,39 +917,36 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_combine_kernel(const De
   };
   const int len_in = p.cache_len[b];
   float m = split_row(lane)[D], l = split_row(lane)[D + 1];
-  float o[kPre][F];
+  feat o[kPre];
 #pragma unroll
-  for (int k = 0; k < kPre; ++k)
-#pragma unroll
-    for (int f = 0; f < F; ++f) o[k][f] = split_row(k)[lane + kWave * f];
+  for (int k = 0; k < kPre; ++k) o[k] = *reinterpret_cast<const feat *>(split_row(k) + F * lane);
 
-  const int len = clamp_len(p, kPaged, len_in), chunk = max(chunk_keys(p, len), 1);
-  const int used = max((len + chunk - 1) / chunk, 1);   // (an empty sequence writes one empty split)
-  const int cnt = (used - part + kHeadWaves - 1) / kHeadWaves;
-  float M = -FLT_MAX, L = 0.f, O[F];
-#pragma unroll
-  for (int f = 0; f < F; ++f) O[f] = 0.f;
-  for (int i0 = 0; i0 < cnt; i0 += kWave) {
+  const int len = clamp_len(p, kPaged, len_in), chunk = chunk_keys(p, len);
+  // Whether the wave's i-th split has keys (an empty sequence writes one empty split).
+  auto written = [&](int i) -> bool {
+    const int split = i * kHeadWaves + part;
+    return split < p.n_split && (split == 0 || static_cast<int64_t>(split) * chunk < len);
+  };
+  float M = -FLT_MAX, L = 0.f;
+  feat O = {};
+  for (int i0 = 0; written(i0); i0 += kWave) {
     if (i0 > 0) {
       m = split_row(i0 + lane)[D];
       l = split_row(i0 + lane)[D + 1];
     }
-    const bool valid = i0 + lane < cnt && l > 0.f;
-    float mx = valid ? m : -FLT_MAX;
-    mx = fmaxf(M, wave_max(mx));
+    const bool in = written(i0 + lane);
+    const int n = __popcll(__ballot(in));
+    const bool valid = in && l > 0.f;
+    const float mx = fmaxf(M, wave_max(valid ? m : -FLT_MAX));
     const float corr = exp2_fast(M - mx);
     M = mx;
     const float w = valid ? exp2_fast(m - M) : 0.f;
     L = fmaf(L, corr, wave_sum(valid ? l * w : 0.f));
-#pragma unroll
-    for (int f = 0; f < F; ++f) O[f] *= corr;
-    const int n = min(kWave, cnt - i0);
+    O *= corr;
     for (int k0 = 0; k0 < n; k0 += kPre) {
       if (i0 + k0 > 0) {
 #pragma unroll
-        for (int k = 0; k < kPre; ++k)
-#pragma unroll
-          for (int f = 0; f < F; ++f) o[k][f] = split_row(i0 + k0 + k)[lane + kWave * f];
+        for (int k = 0; k < kPre; ++k) o[k] = *reinterpret_cast<const feat *>(split_row(i0 + k0 + k) + F * lane);
       }
 #pragma unroll
       for (int k = 0; k < kPre; ++k) {
@@ -923,28 +958,38 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_combine_kernel(const De
     }
   }
   if constexpr (kHeadWaves > 1) {
-    static_assert(kHeadWaves == kWaves, "a workgroup's waves share one head");
-    __shared__ float s_m[kWaves], s_l[kWaves], s_o[kWaves][D];
+    static_assert(kHeadWaves == kBlockWaves, "a workgroup's waves share one head");
+    __shared__ float s_m[kBlockWaves], s_l[kBlockWaves], s_o[kBlockWaves][D];
     if (lane == 0) {
       s_m[wave] = M;
       s_l[wave] = L;
     }
 #pragma unroll
-    for (int f = 0; f < F; ++f) s_o[wave][lane + kWave * f] = O[f];
+    for (int f = 0; f < F; ++f) s_o[wave][F * lane + f] = O[f];
     __syncthreads();
     if (threadIdx.x >= D) return;
+    float ms[kBlockWaves], ls[kBlockWaves], os[kBlockWaves];
+#pragma unroll
+    for (int w = 0; w < kBlockWaves; ++w) {
+      ms[w] = s_m[w];
+      ls[w] = s_l[w];
+      os[w] = s_o[w][threadIdx.x];
+    }
     M = -FLT_MAX;
-    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w]);
+#pragma unroll
+    for (int w = 0; w < kBlockWaves; ++w) M = fmaxf(M, ms[w]);
     float Ls = 0.f, Os = 0.f;
-    for (int w = 0; w < kWaves; ++w) {
-      const float wt = exp2_fast(s_m[w] - M);
-      Ls = fmaf(s_l[w], wt, Ls);
-      Os = fmaf(s_o[w][threadIdx.x], wt, Os);
+#pragma unroll
+    for (int w = 0; w < kBlockWaves; ++w) {
+      const float wt = exp2_fast(ms[w] - M);
+      Ls = fmaf(ls[w], wt, Ls);
+      Os = fmaf(os[w], wt, Os);
     }
     p.out[head * D + threadIdx.x] = Ls > 0.f ? Os / Ls : 0.f;
   } else {
 #pragma unroll
-    for (int f = 0; f < F; ++f) p.out[head * D + lane + kWave * f] = L > 0.f ? O[f] / L : 0.f;
+    for (int f = 0; f < F; ++f) O[f] = L > 0.f ? O[f] / L : 0.f;
+    *reinterpret_cast<feat *>(p.out + head * D + F * lane) = O;
   }
 }
 
@@ -971,8 +1016,10 @@ hipError_t launch_split(const DecodeParams &in, hipStream_t stream) {
   const int64_t heads = static_cast<int64_t>(p.batch) * p.n_q_heads;
   if (p.n_split <= kPre)
     decode_combine_kernel<D, kPaged, 1><<<static_cast<unsigned>((heads + kWaves - 1) / kWaves), kWaves * kWave, 0, stream>>>(p);
-  else
+  else if (p.n_split <= 2 * kPre * kWaves)
     decode_combine_kernel<D, kPaged, kWaves><<<static_cast<unsigned>(heads), kWaves * kWave, 0, stream>>>(p);
+  else
+    decode_combine_kernel<D, kPaged, 16><<<static_cast<unsigned>(heads), 16 * kWave, 0, stream>>>(p);
   return hipGetLastError();
 }
 
