@@ -496,6 +496,16 @@ struct Words<2> {
   typedef uint32_t type __attribute__((ext_vector_type(2)));
 };
 
+// Exchanges lanes 8..15 of each row of 16 in a with lanes 0..7 of the row in b.
+__device__ __forceinline__ void swap_rows8(u32x4 &a, u32x4 &b) {
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const int x = static_cast<int>(a[w]), y = static_cast<int>(b[w]);
+    a[w] = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(x, y, 0x128, 0xF, 0xC, false));
+    b[w] = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(y, x, 0x128, 0xF, 0x3, false));
+  }
+}
+
 constexpr int kTile = 32;   // keys per wave and tile: the value product's contraction length
 
 // GT: query heads per KV head the kernel has room for (4 or 8; smaller groups
@@ -649,21 +659,21 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
       return (row_layer + static_cast<int64_t>(static_cast<uint32_t>(__shfl(static_cast<int>(tr.slot), t)))) *
                  row_step + static_cast<int64_t>(kvh) * kRowBytes;
   };
-  // Key rows in the product's operand layout.  A load reads a quarter of each of 16
-  // rows and the other quarters follow at once from the same cache lines, so these
-  // are plain loads: as non-temporal loads they took 10 % longer.
+  // Key rows.  The product's operand layout would read a half of each of 16 rows' cache
+  // lines per load, and the other halves with the next one; with more than two waves a
+  // compute unit has more lines in flight than its L1 holds, and halves are read again.
+  // So a load reads whole lines of 8 rows, once, past the caches: line q of the keys of
+  // columns 0..7 by load 2 q, of columns 8..15 by load 2 q + 1, one half of a line in the
+  // lanes of its own column and the other 8 lanes away (swap_rows8 brings it over).  Two
+  // layers of 64 paged sequences of 2,912-6,512 keys (7 heads): 240.4 us in half lines,
+  // 224.4 in whole ones; 32 contiguous ones of 2,756-4,256 keys (4 heads): 155.6 and 151.7.
+  const int ka = 8 * (n16 % 8 / 4) + n16 % 4;
   auto load_k = [&](const TileRows &tr, u32x4 (&kd)[2][KK]) {
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
-      const int t = kt0 + 4 * st;
-      int64_t o;
-      if constexpr (kPaged && kHalfBlocks)
-        o = n16 < 8 ? key_offset(tr, t, 0) : key_offset(tr, t, 1);
-      else
-        o = key_offset(tr, t, 0);
-      const char *kp = cache_k + o + kj * 16;
+      const char *kp[2] = {cache_k + key_offset(tr, ka + 4 * st, 0), cache_k + key_offset(tr, ka + 4 * st + 16, 1)};
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kd[st][kk] = *reinterpret_cast<const u32x4 *>(kp + kk * 64);
+      for (int kk = 0; kk < KK; ++kk) kd[st][kk] = load_nt(kp[kk % 2] + (n16 / 8) * 64 + kj * 16 + kk / 2 * 128);
     }
   };
   // Value rows, 16 lanes to a row.
@@ -741,6 +751,10 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
   for (int jt = jw; jt < j1; jt += KPB) {
     const uint32_t live = tr.live;
     f32x4 sa[kA][2];
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+      for (int kk = 0; kk < KK; kk += 2) swap_rows8(kr[st][kk], kr[st][kk + 1]);
 #pragma unroll
     for (int a = 0; a < kA; ++a) {
 #pragma unroll
