@@ -6,9 +6,9 @@
 //
 // Split-K flash decoding.  Kernel 1: one workgroup per (key chunk, KV head,
 // sequence) streams its keys and values once for all G query heads of the
-// group, and the sequence's keys are split evenly over its workgroups, about as
-// many workgroups in all as the chip holds at once (with at most 64 sequences,
-// the grid's sequence rows take the sequences longest first).  bf16 caches run both
+// group, and the sequence's keys are split evenly over its workgroups (plan_splits;
+// with at most 64 sequences, the grid's sequence rows take the sequences longest
+// first).  bf16 caches run both
 // contractions on the matrix cores, 32 keys at a time (decode_partial_bf16_kernel);
 // float32 caches take a 16-byte chunk of a key row per lane with scores reduced
 // across the lanes of a row by DPP lane permutations (decode_partial_kernel).
@@ -16,6 +16,7 @@
 // maximum rose.  The workgroup's waves are merged in LDS and one (max, sum,
 // weighted V) partial per query head and chunk is written to the caller's
 // workspace.  Kernel 2 merges the chunks.
+#include <algorithm>
 #include <cfloat>
 #include <climits>
 #include <cmath>
@@ -30,14 +31,12 @@ namespace {
 #ifndef PRCR_DEC_ITERS
 #define PRCR_DEC_ITERS 2
 #endif
-#ifndef PRCR_DEC_WORKGROUPS
-#define PRCR_DEC_WORKGROUPS 0    // workgroups per call; 0: as many as are resident at once
-#endif
 #ifndef PRCR_DEC_WAVES
 #define PRCR_DEC_WAVES 4
 #endif
 constexpr int kWaves = PRCR_DEC_WAVES;
 constexpr int kIters = PRCR_DEC_ITERS;   // key rows per lane group in flight
+constexpr int kUnits = 256;              // compute units of the chip
 
 template <typename T>
 struct Elems;
@@ -103,6 +102,7 @@ __device__ __forceinline__ void lds_barrier() {
 // rank is the number of keys (length, then lower index) above its own, and wave w counts
 // among sequences 16 w to 16 w + 15.  With 64 sequences every wave counting all of them
 // took 2.7 us (two compares each) or 1.1 us (one); the shared count takes 0.6.
+template <int kWaves>
 __device__ __forceinline__ int sequence_of_row(const DecodeParams &p, int lane, int z, int *len) {
   if (p.batch > kWave) {
     *len = p.cache_len[z];
@@ -140,11 +140,28 @@ __device__ __forceinline__ int sequence_of_row(const DecodeParams &p, int lane, 
   return b;
 }
 
+// The bf16 kernel's grid is (KV head, row, split): the first workgroups to be placed are the
+// first chunks of all sequences, and the ones without keys come last.  (With the splits
+// innermost, the workgroups with keys of a sequence of 4,000 in a cache of 63 splits shared
+// every second compute unit: 11.1 us a layer, now 9.3.)  Every second round of workgroups over
+// the chip takes the rows in reverse, so that a compute unit's second workgroup
+// is short where its first is long: two layers of 64 paged sequences of 2,912-6,512 keys
+// in two splits took 230.0 us with the splits innermost, 243.2 with the rows in the same
+// order in both splits and 215.7 this way.  The float32 kernel has three rounds, and is
+// faster with the splits innermost (238.8 against 257.3 us, 32 such sequences, 4 heads).
+__device__ __forceinline__ int row_of(const DecodeParams &p, int split) {
+  const int y = static_cast<int>(blockIdx.y);
+  const int pairs = static_cast<int>(gridDim.x * gridDim.y);
+  return ((split * pairs + pairs / 2) / kUnits) & 1 ? p.batch - 1 - y : y;
+}
+
 // Keys per workgroup of a sequence of len keys: an even share of its n_split workgroups,
 // in whole rounds of p.round keys, so that no workgroup of a sequence waits on a longer
-// one.  Workgroups past the sequence's last key have nothing to do and write nothing.
+// one; no fewer than p.min_keys where p.fill workgroups would do (plan_splits).
+// Workgroups past the sequence's last key have nothing to do and write nothing.
 __device__ __forceinline__ int chunk_keys(const DecodeParams &p, int len) {
-  const int per = (len + p.n_split - 1) / p.n_split;
+  int per = (len + p.n_split - 1) / p.n_split;
+  if (p.n_split > p.fill && per < p.min_keys) per = (len + p.fill - 1) / p.fill;
   return (per + p.round - 1) & -p.round;   // (a power of two)
 }
 
@@ -162,7 +179,7 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // at
 // workspace for decode_combine_kernel, or, where every sequence is one chunk (p.direct), to
 // the output at once.  Four features of one head per thread, every LDS read issued before
 // the first use; a feature at a time this took 0.6 us of the 4 us that a short chunk takes.
-template <int D, int GT, int kParts, int kStep, int kRows>
+template <int kWaves, int D, int GT, int kParts, int kStep, int kRows>
 __device__ __forceinline__ void finish_split(const DecodeParams &p, int b, int kvh, int G, int split,
                                              const float (&s_m)[kWaves][GT], const float (&s_l)[kWaves][GT],
                                              const float (&s_o)[kWaves][kRows][D]) {
@@ -225,7 +242,7 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
   const int split = blockIdx.x, kvh = blockIdx.y;
   const int lane = threadIdx.x & (kWave - 1);
   int len_in;
-  const int b = sequence_of_row(p, lane, blockIdx.z, &len_in);
+  const int b = sequence_of_row<kWaves>(p, lane, blockIdx.z, &len_in);
   const int wave = threadIdx.x / kWave;
   const int kg = lane / LPK;                 // key row slot within the wave
   const int c = lane % LPK;                  // 16-byte chunk of the row
@@ -414,7 +431,7 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
     }
   }
   __syncthreads();
-  finish_split<D, GT, 1, 1>(p, b, kvh, G, split, s_m, s_l, s_o);
+  finish_split<kWaves, D, GT, 1, 1>(p, b, kvh, G, split, s_m, s_l, s_o);
 }
 
 // ---------------------------------------------------------------------------
@@ -512,7 +529,8 @@ constexpr int kTile = 32;   // keys per wave and tile: the value product's contr
 // repeat their first head).  kHalfBlocks (paged only): block_size is a multiple of
 // 16, so that each half of a tile (tiles start at multiples of 32) lies in one
 // block; other block sizes look every key up.
-template <int D, int GT, bool kPaged, bool kHalfBlocks>
+// kWaves: waves per workgroup, 4, or 2 where the whole cache is few chunks (plan_splits).
+template <int D, int GT, bool kPaged, bool kHalfBlocks, int kWaves>
 __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void decode_partial_bf16_kernel(const DecodeParams p) {
   constexpr int KK = D / 32;                 // products over the head dim per 16 keys
   constexpr int kA = GT / 4;                 // query operands: 4 heads x (3 parts + 1 unused row)
@@ -540,11 +558,11 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
   __shared__ float s_l[kWaves][GT];
   __shared__ __align__(16) float s_o[kWaves][16][D];
 
-  const int split = blockIdx.x, kvh = blockIdx.y;
+  const int split = blockIdx.z, kvh = blockIdx.x;
   const int lane = threadIdx.x & (kWave - 1);
   const double inv = p.inv_freq[threadIdx.x % P];
   int len_in;
-  const int b = sequence_of_row(p, lane, blockIdx.z, &len_in);
+  const int b = sequence_of_row<kWaves>(p, lane, row_of(p, split), &len_in);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int n16 = lane % 16;                 // product column; operand row
   const int kj = lane / 16;                  // k group of the operands; head of the lane's scores
@@ -882,7 +900,7 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
           f32x4{acc[4 * c][r], acc[4 * c + 1][r], acc[4 * c + 2][r], acc[4 * c + 3][r]};
   }
   __syncthreads();
-  finish_split<D, GT, GT == 4 ? 3 : 2, GT>(p, b, kvh, G, split, s_m, s_l, s_o);
+  finish_split<kWaves, D, GT, GT == 4 ? 3 : 2, GT>(p, b, kvh, G, split, s_m, s_l, s_o);
 }
 
 // Over the wave's four rows of 16 lanes (the same value in every lane): register lane
@@ -1007,24 +1025,34 @@ __global__ __launch_bounds__((kHeadWaves > kWaves ? kHeadWaves : kWaves) * kWave
   }
 }
 
+template <int D, int GT, bool kPaged, int kW>
+void launch_bf16(const DecodeParams &p, hipStream_t stream) {
+  const dim3 grid(p.n_kv_heads, p.batch, p.n_split), block(kW * kWave);
+  if constexpr (kPaged) {
+    if (p.block_size % 16 == 0)
+      decode_partial_bf16_kernel<D, GT, true, true, kW><<<grid, block, 0, stream>>>(p);
+    else
+      decode_partial_bf16_kernel<D, GT, true, false, kW><<<grid, block, 0, stream>>>(p);
+  } else {
+    decode_partial_bf16_kernel<D, GT, false, false, kW><<<grid, block, 0, stream>>>(p);
+  }
+}
+
 template <typename T, int D, int GT, bool kPaged>
 hipError_t launch_split(const DecodeParams &in, hipStream_t stream) {
   DecodeParams p = in;
   // Keys a workgroup's waves take at once: a tile each, or kWave / (D / chunk) rows each.
-  p.round = kWaves * (std::is_same_v<T, uint16_t> ? kTile : kWave / (D / Elems<T>::kPerChunk));
-  const dim3 grid(p.n_split, p.n_kv_heads, p.batch);
   if constexpr (std::is_same_v<T, uint16_t>) {
-    if constexpr (kPaged) {
-      if (p.block_size % 16 == 0)
-        decode_partial_bf16_kernel<D, GT, true, true><<<grid, kWaves * kWave, 0, stream>>>(p);
-      else
-        decode_partial_bf16_kernel<D, GT, true, false><<<grid, kWaves * kWave, 0, stream>>>(p);
-    } else {
-      decode_partial_bf16_kernel<D, GT, false, false><<<grid, kWaves * kWave, 0, stream>>>(p);
-    }
-  } else
+    p.round = p.waves * kTile;
+    if (p.waves == 2)
+      launch_bf16<D, GT, kPaged, 2>(p, stream);
+    else
+      launch_bf16<D, GT, kPaged, 4>(p, stream);
+  } else {
+    p.round = kWaves * (kWave / (D / Elems<T>::kPerChunk));
     decode_partial_kernel<T, D, GT, kPaged>
         <<<dim3(p.n_split, p.n_kv_heads, p.batch), kWaves * kWave, 0, stream>>>(p);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.direct) return e;
   const int64_t heads = static_cast<int64_t>(p.batch) * p.n_q_heads;
@@ -1058,12 +1086,10 @@ hipError_t dispatch_dim(const DecodeParams &p, int head_dim, int G, hipStream_t 
 }  // namespace
 
 int decode_splits(int64_t capacity, int batch, int n_kv_heads, int group) {
-  // About as many workgroups as the chip holds at once, so that all of them
-  // start together and none waits for a second round: 256 compute units with 3
-  // workgroups of the bf16 kernel each (2 with 8 query heads per KV head, whose
-  // kernel holds more registers).  No split of fewer than 64 keys at full
-  // capacity.
-  const int64_t target = PRCR_DEC_WORKGROUPS > 0 ? PRCR_DEC_WORKGROUPS : (group > 4 ? 512 : 768);
+  // Partials that a call has room for.  As many workgroups as the chip holds at once:
+  // 256 compute units with 3 workgroups each (2 with 8 query heads per KV head, whose
+  // bf16 kernel holds more registers).  No split of fewer than 64 keys at full capacity.
+  const int64_t target = group > 4 ? 512 : 768;
   const int64_t pairs = static_cast<int64_t>(batch) * n_kv_heads;
   int64_t ns = (target + pairs - 1) / pairs;
   const int64_t most = (capacity + 63) / 64;
@@ -1078,6 +1104,53 @@ bool overlap(const void *a, double na, const void *b, double nb) {
   const double x = static_cast<double>(reinterpret_cast<uintptr_t>(a));
   const double y = static_cast<double>(reinterpret_cast<uintptr_t>(b));
   return a != nullptr && b != nullptr && x < y + nb && y < x + na;
+}
+
+// How a call is split, within the room for decode_splits' partials (p->n_split on entry).
+// Only the sequence's length and the call's shape enter, so that a sequence's result does
+// not depend on the others'.
+//
+// float32: all of them.  That kernel is bound by its arithmetic and wants every wave slot.
+//
+// bf16.  One workgroup per compute unit reads the cache as fast as more do (two layers of 64
+// sequences of 4,712 keys, 4 KV heads: 197 us with 256 workgroups and no merge, 206 with 512,
+// 208 with 768), so short chunks are merged for nothing: a layer of sequences of 500-800 keys
+// takes 18.9 us in one chunk and 23 in two.  But sequences of different lengths are shared
+// out better in more (2,912-6,512 keys: 236 us in one, 216 in two), so where every chunk
+// keeps 512 keys there are two to four rounds of workgroups over the chip (64 sequences of
+// 2,912-6,512 keys, 2 KV heads: 128 us where chunks had to keep 1,024, 115 with 512).  Either way
+// the count that fills its last round best is taken.  A cache that is at most 256 chunks of
+// 64 keys is read by workgroups of two waves, so that twice as many compute units take part
+// (one sequence of 1,152 keys: 8.4 us a layer with four waves, 7.9 with two; 300 keys: 7.3
+// and 6.7).
+void plan_splits(DecodeParams *p, prcr_dtype dtype, bool paged) {
+  const int64_t room = p->n_split, pairs = static_cast<int64_t>(p->batch) * p->n_kv_heads;
+  const int64_t capacity = paged ? static_cast<int64_t>(p->max_blocks) * p->block_size : p->s_max;
+  constexpr int kMinKeys = 512;
+  p->waves = 4;
+  p->fill = p->n_split;
+  p->min_keys = 0;
+  if (dtype == PRCR_F32) return;
+  auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  // The splits for lo to hi workgroups that come nearest to whole rounds over the chip.
+  auto rounds = [&](int64_t lo, int64_t hi) {
+    int64_t best = ceil_div(lo, pairs);
+    double share = 0;
+    for (int64_t n = best; n <= ceil_div(hi, pairs); ++n) {
+      const double s = static_cast<double>(pairs * n) / static_cast<double>(ceil_div(pairs * n, kUnits) * kUnits);
+      if (s > share + 1e-9) {
+        share = s;
+        best = n;
+      }
+    }
+    return std::min(best, room);
+  };
+  const int64_t fill = pairs >= 3 * kUnits / 4 ? 1 : rounds(3 * kUnits / 4, 2 * kUnits);
+  const int64_t more = rounds(2 * kUnits, 4 * kUnits);
+  p->fill = static_cast<int32_t>(fill);
+  p->n_split = static_cast<int32_t>(capacity / kMinKeys >= more ? std::max(fill, more) : fill);
+  p->min_keys = kMinKeys;
+  if (pairs * ceil_div(capacity, 64) <= kUnits) p->waves = 2;
 }
 
 // Whether the partial kernel may write the outputs itself: every sequence is one chunk,
@@ -1102,6 +1175,7 @@ hipError_t launch_decode(const DecodeParams &in, prcr_dtype dtype, int head_dim,
                          hipStream_t stream) {
   DecodeParams p = in;
   const int G = p.n_q_heads / p.n_kv_heads;
+  plan_splits(&p, dtype, paged);
   p.direct = writes_direct(p, dtype == PRCR_F32 ? 4 : 2, head_dim, paged);
   if (dtype == PRCR_F32)
     return paged ? dispatch_dim<float, true>(p, head_dim, G, stream)

@@ -123,9 +123,12 @@ struct DecodeParams {
   int32_t batch, n_layers, n_kv_heads, n_q_heads, layer;
   int32_t s_max, block_size, max_blocks, n_blocks;
   int32_t block_shift;            // log2(block_size) if a power of two, else -1
-  int32_t n_split;                // workgroups per (sequence, KV head)
-  int32_t round;                  // keys per workgroup come in multiples of this (set by the launcher)
-  int32_t direct;                 // n_split is 1 and the kernel writes out itself (set by the launcher)
+  int32_t n_split;                // workgroups per (sequence, KV head); room for as many until the launcher's plan
+  int32_t fill;                   // splits that give every compute unit a workgroup (this and the rest: the launcher)
+  int32_t min_keys;               // keys a chunk has at least where there are more splits than that
+  int32_t waves;                  // waves per workgroup of the bf16 kernel: 2 or 4
+  int32_t round;                  // keys per workgroup come in multiples of this
+  int32_t direct;                 // n_split is 1 and the kernel writes out itself
   float scale;
   double inv_freq[kMaxPairs];
 };
