@@ -160,8 +160,12 @@ __device__ __forceinline__ int row_of(const DecodeParams &p, int split) {
 // one; no fewer than p.min_keys where p.fill workgroups would do (plan_splits).
 // Workgroups past the sequence's last key have nothing to do and write nothing.
 __device__ __forceinline__ int chunk_keys(const DecodeParams &p, int len) {
-  int per = (len + p.n_split - 1) / p.n_split;
-  if (p.n_split > p.fill && per < p.min_keys) per = (len + p.fill - 1) / p.fill;
+  // ceil(len / n) by the launcher's ceil(2^32 / n): one too many at most (len < 2^30).
+  auto share = [&](int n, uint32_t inverse) -> int {
+    return n == 1 ? len : static_cast<int>(__umulhi(static_cast<uint32_t>(len + n - 1), inverse));
+  };
+  int per = share(p.n_split, p.split_inverse);
+  if (p.n_split > p.fill && per < p.min_keys) per = share(p.fill, p.fill_inverse);
   return (per + p.round - 1) & -p.round;   // (a power of two)
 }
 
@@ -247,7 +251,7 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
   const int kg = lane / LPK;                 // key row slot within the wave
   const int c = lane % LPK;                  // 16-byte chunk of the row
   const int grp = wave * KPW + kg;           // key row slot within the workgroup
-  const int G = p.n_q_heads / p.n_kv_heads;
+  const int G = p.group;
 
   const int len = clamp_len(p, kPaged, len_in);
   if (len != len_in && split == 0 && kvh == 0 && threadIdx.x == 0 && p.err != nullptr)
@@ -566,7 +570,7 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int n16 = lane % 16;                 // product column; operand row
   const int kj = lane / 16;                  // k group of the operands; head of the lane's scores
-  const int G = p.n_q_heads / p.n_kv_heads;
+  const int G = p.group;
 
   const int len = clamp_len(p, kPaged, len_in);
   if (len != len_in && split == 0 && kvh == 0 && threadIdx.x == 0 && p.err != nullptr)
@@ -939,10 +943,10 @@ __global__ __launch_bounds__((kHeadWaves > kWaves ? kHeadWaves : kWaves) * kWave
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int part = wave % kHeadWaves;        // this wave's splits: part, part + kHeadWaves, ...
-  const int64_t heads = static_cast<int64_t>(p.batch) * p.n_q_heads;
-  const int64_t head = static_cast<int64_t>(blockIdx.x) * (kBlockWaves / kHeadWaves) + wave / kHeadWaves;
-  if (head >= heads) return;                 // (whole workgroups only where waves share a head)
-  const int b = static_cast<int>(head / p.n_q_heads);
+  const int b = blockIdx.y;
+  const int qh = static_cast<int>(blockIdx.x) * (kBlockWaves / kHeadWaves) + wave / kHeadWaves;
+  if (qh >= p.n_q_heads) return;             // (whole workgroups only where waves share a head)
+  const int64_t head = static_cast<int64_t>(b) * p.n_q_heads + qh;
   const float *ws = p.ws + head * p.n_split * (D + 2);
   auto split_row = [&](int i) -> const float * {   // the wave's i-th split (clamped: always in the array)
     return ws + static_cast<int64_t>(min(i * kHeadWaves + part, p.n_split - 1)) * (D + 2);
@@ -1055,13 +1059,13 @@ hipError_t launch_split(const DecodeParams &in, hipStream_t stream) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.direct) return e;
-  const int64_t heads = static_cast<int64_t>(p.batch) * p.n_q_heads;
+  const unsigned heads = static_cast<unsigned>(p.n_q_heads), rows = static_cast<unsigned>(p.batch);
   if (p.n_split <= kPre)
-    decode_combine_kernel<D, kPaged, 1><<<static_cast<unsigned>((heads + kWaves - 1) / kWaves), kWaves * kWave, 0, stream>>>(p);
+    decode_combine_kernel<D, kPaged, 1><<<dim3((heads + kWaves - 1) / kWaves, rows), kWaves * kWave, 0, stream>>>(p);
   else if (p.n_split <= 2 * kPre * kWaves)
-    decode_combine_kernel<D, kPaged, kWaves><<<static_cast<unsigned>(heads), kWaves * kWave, 0, stream>>>(p);
+    decode_combine_kernel<D, kPaged, kWaves><<<dim3(heads, rows), kWaves * kWave, 0, stream>>>(p);
   else
-    decode_combine_kernel<D, kPaged, 16><<<static_cast<unsigned>(heads), 16 * kWave, 0, stream>>>(p);
+    decode_combine_kernel<D, kPaged, 16><<<dim3(heads, rows), 16 * kWave, 0, stream>>>(p);
   return hipGetLastError();
 }
 
@@ -1176,6 +1180,10 @@ hipError_t launch_decode(const DecodeParams &in, prcr_dtype dtype, int head_dim,
   DecodeParams p = in;
   const int G = p.n_q_heads / p.n_kv_heads;
   plan_splits(&p, dtype, paged);
+  auto inverse = [](int64_t n) { return n > 1 ? static_cast<uint32_t>(((int64_t{1} << 32) + n - 1) / n) : 0u; };
+  p.split_inverse = inverse(p.n_split);
+  p.fill_inverse = inverse(p.fill);
+  p.group = G;
   p.direct = writes_direct(p, dtype == PRCR_F32 ? 4 : 2, head_dim, paged);
   if (dtype == PRCR_F32)
     return paged ? dispatch_dim<float, true>(p, head_dim, G, stream)
