@@ -89,6 +89,22 @@ struct StoreParams {
   int32_t row_bytes;              // n_kv_heads * head_dim * element size
 };
 
+// Division of numbers below 2^31 by a number from 1 to 2^31 - 1 that the host knows: with
+// 2^(l - 1) < d <= 2^l and m = ceil(2^(31 + l) / d) < 2^32, m d exceeds 2^(31 + l) by less
+// than d, so that n m / 2^(31 + l) is n / d plus less than 1 / d.
+struct Divisor {
+  uint32_t multiplier;
+  int32_t shift;
+  static Divisor of(int32_t d) {
+    int l = 0;
+    while ((int64_t{1} << l) < d) ++l;
+    return {static_cast<uint32_t>(((uint64_t{1} << (31 + l)) + d - 1) / static_cast<uint64_t>(d)), 31 + l};
+  }
+  __host__ __device__ uint32_t divide(uint32_t n) const {
+    return static_cast<uint32_t>((static_cast<uint64_t>(n) * multiplier) >> shift);
+  }
+};
+
 struct PrefillParams {
   const void *raw_k;
   const void *raw_v;
@@ -108,6 +124,8 @@ struct PrefillParams {
   int32_t batch, s_src, max_visual, n_layers, n_kv_heads, layer, write_coords;
   int32_t s_max, block_size, max_blocks, n_blocks;
   double inv_freq[kMaxPairs];
+  bool rows32;                    // batch * s_src * n_kv_heads < 2^31: the rows' indices by these (launcher)
+  Divisor by_seq, by_head, by_block;
 };
 
 struct DecodeParams {
