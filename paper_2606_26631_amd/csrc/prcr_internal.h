@@ -34,6 +34,22 @@ struct Interleaved {
   }
 };
 
+// Division of numbers below 2^31 by a number from 1 to 2^31 - 1 that the host knows: with
+// 2^(l - 1) < d <= 2^l and m = ceil(2^(31 + l) / d) < 2^32, m d exceeds 2^(31 + l) by less
+// than d, so that n m / 2^(31 + l) is n / d plus less than 1 / d.
+struct Divisor {
+  uint32_t multiplier;
+  int32_t shift;
+  static Divisor of(int32_t d) {
+    int l = 0;
+    while ((int64_t{1} << l) < d) ++l;
+    return {static_cast<uint32_t>(((uint64_t{1} << (31 + l)) + d - 1) / static_cast<uint64_t>(d)), 31 + l};
+  }
+  __host__ __device__ uint32_t divide(uint32_t n) const {
+    return static_cast<uint32_t>((static_cast<uint64_t>(n) * multiplier) >> shift);
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Kernel parameter blocks (passed by value as kernel arguments).
 // ---------------------------------------------------------------------------
@@ -68,6 +84,7 @@ struct RebindParams {
   int32_t s_max, block_size, max_blocks, n_blocks;
   int32_t rows_per_wave;          // rows (layer, head) of one token handled by one wave
   int32_t n_row_groups;           // ceil(n_layers * n_kv_heads / rows_per_wave)
+  Divisor by_tblk, by_heads, by_block;   // token blocks, n_kv_heads, block_size (launcher)
   // Fused revisit only (positions computed in the kernel instead of read):
   const int32_t *coords;          // [batch][max_visual][3]
   const int32_t *p_txt;           // [batch]
@@ -87,22 +104,6 @@ struct StoreParams {
   int32_t *err;
   int32_t batch, max_visual, n_layers, n_kv_heads, layer, s_src;
   int32_t row_bytes;              // n_kv_heads * head_dim * element size
-};
-
-// Division of numbers below 2^31 by a number from 1 to 2^31 - 1 that the host knows: with
-// 2^(l - 1) < d <= 2^l and m = ceil(2^(31 + l) / d) < 2^32, m d exceeds 2^(31 + l) by less
-// than d, so that n m / 2^(31 + l) is n / d plus less than 1 / d.
-struct Divisor {
-  uint32_t multiplier;
-  int32_t shift;
-  static Divisor of(int32_t d) {
-    int l = 0;
-    while ((int64_t{1} << l) < d) ++l;
-    return {static_cast<uint32_t>(((uint64_t{1} << (31 + l)) + d - 1) / static_cast<uint64_t>(d)), 31 + l};
-  }
-  __host__ __device__ uint32_t divide(uint32_t n) const {
-    return static_cast<uint32_t>((static_cast<uint64_t>(n) * multiplier) >> shift);
-  }
 };
 
 struct PrefillParams {
