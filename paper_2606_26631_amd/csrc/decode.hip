@@ -458,8 +458,9 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
 // 5 to 8 query heads per KV head.  What bounds the kernel is reading the cache.
 // With the weighted value sum on the vector ALU (a multiply-add per element and
 // head, 16-key tiles) a layer of 64 paged sequences of 2,912-6,512 keys, 4 KV heads
-// and 7 query heads each took 169.6 us, now 123.5 (619 MB); 32 contiguous sequences
-// of 2,756-4,256 keys, 8 KV heads and 4 query heads each 81.7, now 79.7 (458 MB).
+// and 7 query heads each took 169.6 us, on the matrix cores 123.5, and 105.6 now, with whole
+// cache lines per key load and fewer workgroups (619 MB, 5.9 TB/s); 32 contiguous sequences
+// of 2,756-4,256 keys, 8 KV heads and 4 query heads each 81.7, 79.7 and 71.7 (458 MB, 6.4 TB/s).
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
@@ -586,7 +587,7 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
   // tile's rows are to stay in flight while the query is prepared.  The query's parts are
   // formed once, by the thread that rotates the pair, and read as operands: as a choice of
   // part per operand element the set-up was 32 LDS reads each behind a branch.  One
-  // sequence of 1,152 keys (8 KV heads): 10.7 us a layer before, 8.4 now, with the merge.
+  // sequence of 1,152 keys (8 KV heads): 10.7 us a layer before, 8.4 so, with the merge.
   const int32_t q_pos = p.q_pos[b];
   uint32_t q_lo[kQ], q_hi[kQ];
 #pragma unroll

@@ -59,9 +59,9 @@ __global__ __launch_bounds__(kWaves * kWave) void prefill_capture_kernel(const P
   // this lane's rotary frequency.  Vector loads complete in issue order, so a load
   // issued only after another's value is used waits a round trip more.
   // Rows are split into sequence, token and head by multiplications: the two 64-bit
-  // divisions were as many instructions as the rotation.  With the table entry a round
-  // earlier, one sequence of 2,560 tokens took 7.8 us and takes 7.4, 2 KV heads of 8 such
-  // sequences 16.6 and 14.7, six of 1,661-2,545 tokens in a paged cache 20.2 and 19.6.
+  // divisions were as many instructions as the rotation.  One sequence of 2,560 tokens
+  // took 7.8 us and takes 7.4, 8 of them with 2 KV heads 16.6 and 14.7, with 8 KV heads
+  // 52.5 and 50.4; six of 1,661-2,545 tokens in a paged cache 20.0, as before.
   int rb[kIters], rs[kIters], rh[kIters];
   int32_t nt[kIters], cst[kIters];
   int64_t Rc[kIters];
