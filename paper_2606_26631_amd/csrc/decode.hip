@@ -151,8 +151,8 @@ __device__ __forceinline__ int sequence_of_row(const DecodeParams &p, int lane, 
 // faster with the splits innermost (238.8 against 257.3 us, 32 such sequences, 4 heads).
 __device__ __forceinline__ int row_of(const DecodeParams &p, int split) {
   const int y = static_cast<int>(blockIdx.y);
-  const int pairs = static_cast<int>(gridDim.x * gridDim.y);
-  return ((split * pairs + pairs / 2) / kUnits) & 1 ? p.batch - 1 - y : y;
+  const uint32_t before = static_cast<uint32_t>(split) * gridDim.x * gridDim.y;   // workgroups of earlier splits
+  return before / kUnits & 1 ? p.batch - 1 - y : y;
 }
 
 // Keys per workgroup of a sequence of len keys: an even share of its n_split workgroups,
@@ -1137,11 +1137,12 @@ void plan_splits(DecodeParams *p, prcr_dtype dtype, bool paged) {
   p->min_keys = 0;
   if (dtype == PRCR_F32) return;
   auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
-  // The splits for lo to hi workgroups that come nearest to whole rounds over the chip.
+  // The first splits for lo to hi workgroups that come within 3 % of whole rounds over the
+  // chip, or else the nearest (a search of at most some tens of steps, on every call).
   auto rounds = [&](int64_t lo, int64_t hi) {
     int64_t best = ceil_div(lo, pairs);
     double share = 0;
-    for (int64_t n = best; n <= ceil_div(hi, pairs); ++n) {
+    for (int64_t n = best; n <= std::min(ceil_div(hi, pairs), room) && share < 0.97; ++n) {
       const double s = static_cast<double>(pairs * n) / static_cast<double>(ceil_div(pairs * n, kUnits) * kUnits);
       if (s > share + 1e-9) {
         share = s;
@@ -1151,9 +1152,10 @@ void plan_splits(DecodeParams *p, prcr_dtype dtype, bool paged) {
     return std::min(best, room);
   };
   const int64_t fill = pairs >= 3 * kUnits / 4 ? 1 : rounds(3 * kUnits / 4, 2 * kUnits);
-  const int64_t more = rounds(2 * kUnits, 4 * kUnits);
+  const int64_t most = capacity / kMinKeys;
+  const int64_t more = most >= std::min(ceil_div(2 * kUnits, pairs), room) ? rounds(2 * kUnits, 4 * kUnits) : fill;
   p->fill = static_cast<int32_t>(fill);
-  p->n_split = static_cast<int32_t>(capacity / kMinKeys >= more ? std::max(fill, more) : fill);
+  p->n_split = static_cast<int32_t>(most >= more ? std::max(fill, more) : fill);
   p->min_keys = kMinKeys;
   if (pairs * ceil_div(capacity, 64) <= kUnits) p->waves = 2;
 }
