@@ -315,7 +315,8 @@ prcr_status prcr_revisit(const prcr_rope *rope, const prcr_mem *mem,
  *                 owned by the caller (split-K partial results; no state is kept)
  *   scale         usually 1/sqrt(head_dim)
  * Scores and the softmax are accumulated in float32; the query is rotated in
- * double and rounded to float32 once.  cache_len[b] = 0 gives out = 0.  A
+ * double and rounded to float32 once.  cache_len[b] = 0 gives out = 0.  A NaN in
+ * a key below the length, or in a query, makes its heads' outputs NaN.  A
  * cache_len beyond the capacity is clamped with PRCR_DERR_CAPACITY; a block-table
  * entry outside the pool skips its keys with PRCR_DERR_BLOCK.  The capacity per
  * sequence (s_max, or max_blocks * block_size) is at most 2^30 slots, else

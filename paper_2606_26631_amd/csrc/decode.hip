@@ -217,7 +217,7 @@ __device__ __forceinline__ void finish_split(const DecodeParams &p, int b, int k
     }
     if (p.direct) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) O[e] = L > 0.f ? O[e] / L : 0.f;
+      for (int e = 0; e < 4; ++e) O[e] = L != 0.f ? O[e] / L : 0.f;   // (a NaN stays one)
       *reinterpret_cast<f32x4_any *>(p.out + (head0 + g) * D + d) = O;
     } else {
       float *ws = p.ws + ((head0 + g) * p.n_split + split) * (D + 2);
@@ -973,7 +973,7 @@ __global__ __launch_bounds__((kHeadWaves > kWaves ? kHeadWaves : kWaves) * kWave
     }
     const bool in = written(i0 + lane);
     const int n = __popcll(__ballot(in));
-    const bool valid = in && l > 0.f;
+    const bool valid = in && l != 0.f;   // (a split with a NaN key counts: its NaN reaches L)
     const float mx = fmaxf(M, wave_max(valid ? m : -FLT_MAX));
     const float corr = exp2_fast(M - mx);
     M = mx;
@@ -1022,10 +1022,10 @@ __global__ __launch_bounds__((kHeadWaves > kWaves ? kHeadWaves : kWaves) * kWave
       Ls = fmaf(ls[w], wt, Ls);
       Os = fmaf(os[w], wt, Os);
     }
-    p.out[head * D + threadIdx.x] = Ls > 0.f ? Os / Ls : 0.f;
+    p.out[head * D + threadIdx.x] = Ls != 0.f ? Os / Ls : 0.f;
   } else {
 #pragma unroll
-    for (int f = 0; f < F; ++f) O[f] = L > 0.f ? O[f] / L : 0.f;
+    for (int f = 0; f < F; ++f) O[f] = L != 0.f ? O[f] / L : 0.f;
     *reinterpret_cast<feat *>(p.out + head * D + F * lane) = O;
   }
 }
