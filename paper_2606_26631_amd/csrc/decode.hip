@@ -158,7 +158,8 @@ __device__ __forceinline__ int row_of(const DecodeParams &p, int split) {
 // Keys per workgroup of a sequence of len keys: an even share of its n_split workgroups,
 // in whole rounds of p.round keys, so that no workgroup of a sequence waits on a longer
 // one; no fewer than p.min_keys where p.fill workgroups would do (plan_splits).
-// Workgroups past the sequence's last key have nothing to do and write nothing.
+// Workgroups past the sequence's last key have nothing to do and write nothing (with
+// p.all_splits: an empty partial).
 __device__ __forceinline__ int chunk_keys(const DecodeParams &p, int len) {
   // ceil(len / n) by the launcher's ceil(2^32 / n): one too many at most (len < 2^30).
   auto share = [&](int n, uint32_t inverse) -> int {
@@ -259,7 +260,7 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
   const int chunk = chunk_keys(p, len);
   const int j0 = static_cast<int>(min(static_cast<int64_t>(len), static_cast<int64_t>(split) * chunk));
   const int j1 = static_cast<int>(min(static_cast<int64_t>(len), static_cast<int64_t>(j0) + chunk));
-  if (j0 >= j1 && split > 0) return;
+  if (j0 >= j1 && split > 0 && !p.all_splits) return;
 
   // Rotated, scaled query chunk of every head of the group: the lane's elements
   // e = c*EPL .. c*EPL+EPL-1 pair with e +/- D/2, which sits in chunk c +/- LPK/2.
@@ -579,7 +580,7 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
   const int chunk = chunk_keys(p, len);
   const int j0 = static_cast<int>(min(static_cast<int64_t>(len), static_cast<int64_t>(split) * chunk));
   const int j1 = static_cast<int>(min(static_cast<int64_t>(len), static_cast<int64_t>(j0) + chunk));
-  if (j0 >= j1 && split > 0) return;
+  if (j0 >= j1 && split > 0 && !p.all_splits) return;
 
   // What a short sequence pays for is the chain of dependent loads and the query's set-up.
   // The lengths are read once for the order and the length; then the query's rows, then
@@ -959,10 +960,11 @@ __global__ __launch_bounds__((kHeadWaves > kWaves ? kHeadWaves : kWaves) * kWave
   for (int k = 0; k < kPre; ++k) o[k] = *reinterpret_cast<const feat *>(split_row(k) + F * lane);
 
   const int len = clamp_len(p, kPaged, len_in), chunk = chunk_keys(p, len);
-  // Whether the wave's i-th split has keys (an empty sequence writes one empty split).
+  // Whether the wave's i-th split has keys (an empty sequence writes one empty split).  With
+  // p.all_splits the length is not used: its bytes may already be another workgroup's output.
   auto written = [&](int i) -> bool {
     const int split = i * kHeadWaves + part;
-    return split < p.n_split && (split == 0 || static_cast<int64_t>(split) * chunk < len);
+    return split < p.n_split && (split == 0 || p.all_splits || static_cast<int64_t>(split) * chunk < len);
   };
   float M = -FLT_MAX, L = 0.f;
   feat O = {};
@@ -1188,6 +1190,7 @@ hipError_t launch_decode(const DecodeParams &in, prcr_dtype dtype, int head_dim,
   p.fill_inverse = inverse(p.fill);
   p.group = G;
   p.direct = writes_direct(p, dtype == PRCR_F32 ? 4 : 2, head_dim, paged);
+  p.all_splits = overlap(p.out, 4.0 * p.batch * p.n_q_heads * head_dim, p.cache_len, 4.0 * p.batch);
   if (dtype == PRCR_F32)
     return paged ? dispatch_dim<float, true>(p, head_dim, G, stream)
                  : dispatch_dim<float, false>(p, head_dim, G, stream);

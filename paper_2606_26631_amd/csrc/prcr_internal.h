@@ -150,6 +150,7 @@ struct DecodeParams {
   int32_t waves;                  // waves per workgroup of the bf16 kernel: 2 or 4
   int32_t round;                  // keys per workgroup come in multiples of this
   int32_t direct;                 // n_split is 1 and the kernel writes out itself
+  int32_t all_splits;             // out shares bytes with cache_len: every split writes a partial
   float scale;
   double inv_freq[kMaxPairs];
 };

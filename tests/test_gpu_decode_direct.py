@@ -51,3 +51,33 @@ def test_decode_chunks_written_or_merged(B, H, G, dtype, cap, in_place):
     out = out.cpu().numpy()
     assert not out[0].any()
     assert np.abs(out - ref).max() <= 2e-4
+
+
+# Two waves and four, merges of one wave per head, of four and of sixteen, both element
+# types, and calls of one chunk per sequence (which may then not write the output directly).
+@pytest.mark.parametrize("B,H,G,dtype,cap", [(5, 2, 4, "bf16", 900), (5, 2, 7, "bf16", 9000), (96, 8, 4, "bf16", 300),
+                                             (2, 1, 2, "f32", 9000), (5, 8, 1, "f32", 700)])
+def test_output_over_the_lengths(B, H, G, dtype, cap):
+    """The lengths lie in the output's own memory: the merge's workgroups write there while
+    others still run, so none may read a length.  Same bits as with lengths of their own."""
+    D = 64
+    g = torch.Generator(device=DEV).manual_seed(B + cap)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    rnd = lambda *s: torch.randn(s, generator=g, device=DEV).to(tdt)
+    cache = prcr.Cache(rnd(B, 1, H, cap, D), rnd(B, 1, H, cap, D))
+    q = rnd(B, H * G, D)
+    lens = torch.randint(0, min(cap, 300), (B,), generator=g, device=DEV, dtype=torch.int32)
+    lens[-1] = cap
+    pos = lens.clone()
+    rope = prcr.Rope(D, (8, 12, 12), False, 1e6)
+    words = prcr.decode_workspace_bytes(cache, B, H * G) // 4
+    ref = prcr.decode_attention(rope, cache, 0, q, pos, lens)
+    for at in (0, B * H * G * D // 2 - 1, B * H * G * D - B):
+        print(f"output over the lengths: {B} x {H} G={G} {dtype} capacity {cap} at {at}", flush=True)
+        out = torch.full((B, H * G, D), float("nan"), device=DEV)
+        inside = out.view(torch.int32).view(-1)[at:at + B]
+        inside.copy_(lens)
+        ws = torch.full((words,), float("nan"), device=DEV)
+        prcr.decode_attention(rope, cache, 0, q, pos, inside, out=out, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
