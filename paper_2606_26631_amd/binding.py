@@ -156,6 +156,24 @@ def _stream(stream, device):
     return c_void_p(s.cuda_stream)
 
 
+def _new(shape, dtype, device, stream, given=True):
+    """Memory made for a call on `stream`.  On another stream than torch's current one it is
+    that stream's: a block of the current stream's might still be read there when the kernels
+    write it, and would be handed out again, once the call has dropped it, while they run.
+    What the caller is given is used on the current stream, so it is recorded there."""
+    torch = _torch()
+    current = torch.cuda.current_stream(device)
+    if stream is None or stream.cuda_stream == current.cuda_stream:
+        return torch.empty(shape, dtype=dtype, device=device)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device)
+    with torch.cuda.stream(stream):
+        t = torch.empty(shape, dtype=dtype, device=device)
+    if given:
+        t.record_stream(current)
+    return t
+
+
 def _need(t, name, dtype=None, ndim=None, device=None):
     torch = _torch()
     if not isinstance(t, torch.Tensor):
@@ -348,9 +366,9 @@ def reassign_coords(mem: Memory, sel_off, sel_idx, p_txt, mode: str = "pcr", l_e
     _need(p_txt, "p_txt", torch.int32, 1, mem.device)
     _shape(p_txt, "p_txt", (B,))
     if new_pos is None:
-        new_pos = torch.empty((total_k, 3), dtype=torch.float64, device=mem.device)
+        new_pos = _new((total_k, 3), torch.float64, mem.device, stream)
     if next_pos is None:
-        next_pos = torch.empty((B,), dtype=torch.int32, device=mem.device)
+        next_pos = _new((B,), torch.int32, mem.device, stream)
     _need(new_pos, "new_pos", torch.float64, 2, mem.device)
     _need(next_pos, "next_pos", torch.int32, 1, mem.device)
     _shape(new_pos, "new_pos", (total_k, 3))
@@ -384,9 +402,9 @@ def rebind_inject(rope: Rope, mem: Memory, sel_off, sel_idx, new_pos, cache: Cac
     _shape(new_pos, "new_pos", (total_k, 3))
     _shape(cache_len, "cache_len", (B,))
     if new_cache_len is None:
-        new_cache_len = torch.empty((B,), dtype=torch.int32, device=mem.device)
+        new_cache_len = _new((B,), torch.int32, mem.device, stream)
     if slot_mapping is None:
-        slot_mapping = torch.empty((total_k,), dtype=torch.int64, device=mem.device)
+        slot_mapping = _new((total_k,), torch.int64, mem.device, stream)
     _need(new_cache_len, "new_cache_len", torch.int32, 1, mem.device)
     _need(slot_mapping, "slot_mapping", torch.int64, 1, mem.device)
     _shape(new_cache_len, "new_cache_len", (B,))
@@ -422,16 +440,16 @@ def revisit(rope: Rope, mem: Memory, sel_off, sel_idx, p_txt, cache: Cache, cach
     _shape(p_txt, "p_txt", (B,))
     _shape(cache_len, "cache_len", (B,))
     if new_pos is None and store_positions:
-        new_pos = torch.empty((total_k, 3), dtype=torch.float64, device=mem.device)
+        new_pos = _new((total_k, 3), torch.float64, mem.device, stream)
     if new_pos is not None:
         _need(new_pos, "new_pos", torch.float64, 2, mem.device)
         _shape(new_pos, "new_pos", (total_k, 3))
     if next_pos is None:
-        next_pos = torch.empty((B,), dtype=torch.int32, device=mem.device)
+        next_pos = _new((B,), torch.int32, mem.device, stream)
     if new_cache_len is None:
-        new_cache_len = torch.empty((B,), dtype=torch.int32, device=mem.device)
+        new_cache_len = _new((B,), torch.int32, mem.device, stream)
     if slot_mapping is None:
-        slot_mapping = torch.empty((total_k,), dtype=torch.int64, device=mem.device)
+        slot_mapping = _new((total_k,), torch.int64, mem.device, stream)
     _need(next_pos, "next_pos", torch.int32, 1, mem.device)
     _need(new_cache_len, "new_cache_len", torch.int32, 1, mem.device)
     _need(slot_mapping, "slot_mapping", torch.int64, 1, mem.device)
@@ -535,12 +553,12 @@ def decode_attention(rope: Rope, cache: Cache, layer: int, q, q_pos, cache_len, 
     _need(cache_len, "cache_len", torch.int32, 1, cache.device)
     _shape(cache_len, "cache_len", (B,))
     if out is None:
-        out = torch.empty((B, Hq, D), dtype=torch.float32, device=cache.device)
+        out = _new((B, Hq, D), torch.float32, cache.device, stream)
     _need(out, "out", torch.float32, 3, cache.device)
     _shape(out, "out", (B, Hq, D))
     need = decode_workspace_bytes(cache, B, Hq)
     if workspace is None:
-        workspace = torch.empty((max(need, 4) + 3) // 4, dtype=torch.float32, device=cache.device)
+        workspace = _new(((max(need, 4) + 3) // 4,), torch.float32, cache.device, stream, given=False)
     _need(workspace, "workspace", None, None, cache.device)
     if workspace.numel() * workspace.element_size() < need:
         raise ValueError(f"workspace needs {need} bytes")
@@ -580,7 +598,7 @@ def decode_attention_static(rope: Rope, cache: Cache, layer: int, q, q_pos, cach
     _need(cache_len, "cache_len", torch.int32, 1, cache.device)
     _shape(cache_len, "cache_len", (B,))
     if out is None:
-        out = torch.empty((B, Hq, D), dtype=torch.float32, device=cache.device)
+        out = _new((B, Hq, D), torch.float32, cache.device, stream)
     _need(out, "out", torch.float32, 3, cache.device)
     _shape(out, "out", (B, Hq, D))
     _err(err, cache.device)

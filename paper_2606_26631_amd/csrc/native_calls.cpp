@@ -19,11 +19,15 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <optional>
 
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/StreamGuard.h>
+#include <c10/core/impl/VirtualGuardImpl.h>
 #include <torch/csrc/Device.h>
+#include <torch/csrc/Stream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "prcr.h"
@@ -140,30 +144,59 @@ void no_overlap(const at::Tensor &a, const at::Tensor &b) {
   if (x < y + b.nbytes() && y < x + a.nbytes()) throw Skip();
 }
 
-at::Tensor fresh(at::IntArrayRef shape, at::ScalarType type, at::Device device) {
-  return at::empty(shape, at::TensorOptions().dtype(type).device(device));
-}
-
 at::Device device_of(PyObject *owner) {
   const Ref d = attr(owner, s_device);
   if (!THPDevice_Check(d.get())) throw Skip();
   return reinterpret_cast<THPDevice *>(d.get())->device;
 }
 
-hipStream_t stream_of(PyObject *stream, at::Device device) {
-  PyObject *handle;
-  if (stream == Py_None) {
-    const Ref index(PyLong_FromLong(device.index()));
-    handle = PyObject_CallOneArg(g_raw_stream, index.get());
-  } else {
-    handle = PyObject_GetAttr(stream, s_cuda_stream);
-  }
-  const Ref h(handle);
+hipStream_t handle_of(PyObject *number) {
+  const Ref h(number);
   if (!PyLong_CheckExact(h.get())) throw Skip();
   const unsigned long long v = PyLong_AsUnsignedLongLong(h.get());
   if (v == static_cast<unsigned long long>(-1) && PyErr_Occurred()) throw Skip();
   return reinterpret_cast<hipStream_t>(static_cast<uintptr_t>(v));
 }
+
+// The stream of a call, and the memory made for the call.  On another stream than torch's
+// current one that memory is the other stream's: one of the current stream's blocks might
+// still be read there when the kernels write it, and would be handed out again, once the
+// call has dropped it, while they run.  What the caller is given is used on the current
+// stream, so it is recorded there and is not handed out again before that use.
+class Launch {
+ public:
+  Launch(PyObject *stream, at::Device device) : device_(device) {
+    const Ref index(PyLong_FromLong(device.index()));
+    handle_ = handle_of(PyObject_CallOneArg(g_raw_stream, index.get()));
+    if (stream == Py_None) return;
+    const hipStream_t current = handle_;
+    handle_ = handle_of(PyObject_GetAttr(stream, s_cuda_stream));
+    other_ = handle_ != current;
+    if (other_ && THPStream_Check(stream)) {
+      const THPStream *s = reinterpret_cast<const THPStream *>(stream);
+      on_ = c10::Stream::unpack3(s->stream_id, static_cast<c10::DeviceIndex>(s->device_index),
+                                 static_cast<c10::DeviceType>(s->device_type));
+    }
+  }
+  hipStream_t handle() const { return handle_; }
+  at::Tensor fresh(at::IntArrayRef shape, at::ScalarType type, bool given) const {
+    const auto options = at::TensorOptions().dtype(type).device(device_);
+    if (!other_) return at::empty(shape, options);
+    if (!on_ || on_->device() != device_) throw Skip();   // no stream of torch's
+    const c10::impl::VirtualGuardImpl streams(device_.type());
+    const c10::Stream current = streams.getStream(device_);
+    const c10::StreamGuard guard(*on_);
+    at::Tensor t = at::empty(shape, options);
+    if (given) streams.recordDataPtrOnStream(t.storage().data_ptr(), current);
+    return t;
+  }
+
+ private:
+  at::Device device_;
+  hipStream_t handle_;
+  bool other_ = false;
+  std::optional<c10::Stream> on_;
+};
 
 at::Tensor err_of(PyObject *o, at::Device device) {
   at::Tensor t = tensor_or_none(o);
@@ -260,16 +293,15 @@ struct Selection {
 
 // An output: the caller's tensor, checked, or one made here (inside Unlocked).
 struct Out {
-  Out(PyObject *o, at::ScalarType type_, at::Device device_, at::DimVector shape_)
-      : t(tensor_or_none(o)), type(type_), device(device_), shape(std::move(shape_)) {
+  Out(PyObject *o, at::ScalarType type_, at::Device device, at::DimVector shape_)
+      : t(tensor_or_none(o)), type(type_), shape(std::move(shape_)) {
     if (t.defined()) need(t, type, device, shape);
   }
-  void make() {
-    if (!t.defined()) t = fresh(shape, type, device);
+  void make(const Launch &on) {
+    if (!t.defined()) t = on.fresh(shape, type, true);
   }
   at::Tensor t;
   at::ScalarType type;
-  at::Device device;
   at::DimVector shape;
 };
 
@@ -338,13 +370,13 @@ PyObject *store_raw(Args a) {
   if (raw_v.defined()) need(raw_v, m.k.scalar_type(), m.device, shape);
   need(rows, at::kInt, m.device, {m.c.batch, m.c.max_visual});
   const at::Tensor err = err_of(a[5], m.device);
-  hipStream_t stream = stream_of(a[6], m.device);
+  const Launch on(a[6], m.device);
   const int32_t s_src = to_int32(raw_k.size(1));
   prcr_status st;
   {
     Unlocked u;
     st = prcr_store_raw(&m.c, layer, ptr<void>(raw_k), ptr<void>(raw_v), s_src, ptr<int32_t>(rows),
-                        ptr<int32_t>(err), stream);
+                        ptr<int32_t>(err), on.handle());
   }
   PyObject *failed;
   return done(st, &failed) ? Py_NewRef(Py_True) : failed;
@@ -359,17 +391,17 @@ PyObject *reassign_coords(Args a) {
   const int32_t mode = mode_of(a[4]), l_ext = int32_of(a[5]);
   Out new_pos(a[6], at::kDouble, m.device, {sel.k, 3}), next_pos(a[7], at::kInt, m.device, {m.c.batch});
   const at::Tensor err = err_of(a[8], m.device);
-  hipStream_t stream = stream_of(a[9], m.device);
+  const Launch on(a[9], m.device);
   prcr_status st;
   {
     Unlocked u;
-    new_pos.make();
-    next_pos.make();
+    new_pos.make(on);
+    next_pos.make(on);
     no_overlap(next_pos.t, sel.off);
     no_overlap(next_pos.t, m.n_visual);
     st = prcr_reassign_coords(&m.c, ptr<int32_t>(sel.off), ptr<int32_t>(sel.idx), sel.k, ptr<int32_t>(p_txt),
                               static_cast<prcr_mode>(mode), l_ext, ptr<double>(new_pos.t),
-                              ptr<int32_t>(next_pos.t), ptr<int32_t>(err), stream);
+                              ptr<int32_t>(next_pos.t), ptr<int32_t>(err), on.handle());
   }
   PyObject *failed;
   return done(st, &failed) ? tuple_of(new_pos.t, next_pos.t) : failed;
@@ -387,17 +419,17 @@ PyObject *rebind_inject(Args a) {
   need(cache_len, at::kInt, m.device, {m.c.batch});
   Out new_len(a[7], at::kInt, m.device, {m.c.batch}), slots(a[8], at::kLong, m.device, {sel.k});
   const at::Tensor err = err_of(a[9], m.device);
-  hipStream_t stream = stream_of(a[10], m.device);
+  const Launch on(a[10], m.device);
   prcr_status st;
   {
     Unlocked u;
-    new_len.make();
-    slots.make();
+    new_len.make(on);
+    slots.make(on);
     no_overlap(new_len.t, cache_len);
     no_overlap(new_len.t, sel.off);
     st = prcr_rebind_inject(&rope, &m.c, ptr<int32_t>(sel.off), ptr<int32_t>(sel.idx), sel.k,
                             ptr<double>(new_pos), &cache.c, ptr<int32_t>(cache_len), ptr<int32_t>(new_len.t),
-                            ptr<int64_t>(slots.t), ptr<int32_t>(err), stream);
+                            ptr<int64_t>(slots.t), ptr<int32_t>(err), on.handle());
   }
   PyObject *failed;
   return done(st, &failed) ? tuple_of(new_len.t, slots.t) : failed;
@@ -418,15 +450,15 @@ PyObject *revisit(Args a) {
   Out new_pos(a[9], at::kDouble, m.device, {sel.k, 3}), next_pos(a[10], at::kInt, m.device, {m.c.batch}),
       new_len(a[11], at::kInt, m.device, {m.c.batch}), slots(a[12], at::kLong, m.device, {sel.k});
   const at::Tensor err = err_of(a[13], m.device);
-  hipStream_t stream = stream_of(a[14], m.device);
+  const Launch on(a[14], m.device);
   const bool positions = bool_of(a[15]);
   prcr_status st;
   {
     Unlocked u;
-    if (positions) new_pos.make();
-    next_pos.make();
-    new_len.make();
-    slots.make();
+    if (positions) new_pos.make(on);
+    next_pos.make(on);
+    new_len.make(on);
+    slots.make(on);
     const at::Tensor *next_apart[] = {&p_txt, &cache_len, &sel.off, &m.n_visual, &new_len.t};
     for (const at::Tensor *t : next_apart) no_overlap(next_pos.t, *t);
     const at::Tensor *len_apart[] = {&cache_len, &sel.off, &p_txt};
@@ -434,7 +466,7 @@ PyObject *revisit(Args a) {
     st = prcr_revisit(&rope, &m.c, ptr<int32_t>(sel.off), ptr<int32_t>(sel.idx), sel.k, ptr<int32_t>(p_txt),
                       static_cast<prcr_mode>(mode), l_ext, &cache.c, ptr<int32_t>(cache_len),
                       ptr<double>(new_pos.t), ptr<int32_t>(next_pos.t), ptr<int32_t>(new_len.t),
-                      ptr<int64_t>(slots.t), ptr<int32_t>(err), stream);
+                      ptr<int64_t>(slots.t), ptr<int32_t>(err), on.handle());
   }
   PyObject *failed;
   return done(st, &failed) ? tuple_of(new_pos.t, next_pos.t, new_len.t, slots.t) : failed;
@@ -460,14 +492,14 @@ PyObject *prefill_capture(Args a) {
   need(start, at::kInt, m.device, {B});
   const bool write_coords = bool_of(a[10]);
   const at::Tensor err = err_of(a[11], m.device);
-  hipStream_t stream = stream_of(a[12], m.device);
+  const Launch on(a[12], m.device);
   const int32_t s_src = to_int32(S);
   prcr_status st;
   {
     Unlocked u;
     st = prcr_prefill_capture(&rope, &m.c, layer, ptr<void>(raw_k), ptr<void>(raw_v), s_src, ptr<int32_t>(pos),
                               ptr<int32_t>(n_tokens), ptr<int32_t>(vis), write_coords ? 1 : 0, &cache.c,
-                              ptr<int32_t>(start), ptr<int32_t>(err), stream);
+                              ptr<int32_t>(start), ptr<int32_t>(err), on.handle());
   }
   PyObject *failed;
   return done(st, &failed) ? Py_NewRef(Py_True) : failed;
@@ -491,17 +523,17 @@ PyObject *decode(Args a) {
   at::Tensor ws = kStatic ? at::Tensor() : tensor_or_none(a[8]);
   constexpr int kErr = kStatic ? 8 : 9;
   const at::Tensor err = err_of(a[kErr], cache.device);
-  hipStream_t stream = stream_of(a[kErr + 1], cache.device);
+  const Launch on(a[kErr + 1], cache.device);
   const prcr_dtype dtype = dtype_of(cache.k);
   const int32_t b = to_int32(B), hq = to_int32(Hq), nl = to_int32(cache.n_layers()),
                 h = to_int32(cache.n_kv_heads());
   prcr_status st;
   if constexpr (kStatic) {
     Unlocked u;
-    out.make();
+    out.make(on);
     st = prcr_decode_attention_static(&rope, &cache.c, dtype, b, nl, h, layer, ptr<void>(q), hq,
                                       ptr<int32_t>(q_pos), ptr<int32_t>(cache_len), static_cast<float>(scale),
-                                      ptr<float>(out.t), ptr<int32_t>(err), stream);
+                                      ptr<float>(out.t), ptr<int32_t>(err), on.handle());
   } else {
     size_t bytes = 0;
     if (prcr_decode_workspace_size(&cache.c, b, hq, h, to_int32(D), &bytes) != PRCR_OK) throw Skip();
@@ -510,12 +542,12 @@ PyObject *decode(Args a) {
       if (ws.nbytes() < bytes) throw Skip();
     }
     Unlocked u;
-    out.make();
+    out.make(on);
     if (!ws.defined())
-      ws = fresh({static_cast<int64_t>((std::max(bytes, size_t{4}) + 3) / 4)}, at::kFloat, cache.device);
+      ws = on.fresh({static_cast<int64_t>((std::max(bytes, size_t{4}) + 3) / 4)}, at::kFloat, false);
     st = prcr_decode_attention(&rope, &cache.c, dtype, b, nl, h, layer, ptr<void>(q), hq, ptr<int32_t>(q_pos),
                                ptr<int32_t>(cache_len), static_cast<float>(scale), ptr<float>(out.t),
-                               ptr<void>(ws), ws.nbytes(), ptr<int32_t>(err), stream);
+                               ptr<void>(ws), ws.nbytes(), ptr<int32_t>(err), on.handle());
   }
   PyObject *failed;
   return done(st, &failed) ? wrap(out.t) : failed;
