@@ -10,7 +10,8 @@ Each entry point first offers its call to the native module built from
 csrc/native_calls.cpp, which makes the same checks on the tensors' own fields and
 does the whole call, or does nothing and answers None: for arguments that some check
 refuses, and for the unusual ones (subclasses, numbers that are not plain ints, an active
-function mode).  The Python path below then takes the call and gives the error.  A pass of
+function mode).  The Python path below then takes the call and gives the error.  It takes all
+calls where the module is missing or was built for another torch or Python.  A pass of
 revisit (one sequence, 32 tokens, 36 layers) took 28.2 us, bound by this module's Python, and
 takes 8.1; a reassign + rebind pair on a tiny cache 37.0 and 12.6.
 """
@@ -18,6 +19,8 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import warnings
 from ctypes import POINTER, c_double, c_int, c_int32, c_void_p
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libprcr.so")
@@ -113,15 +116,31 @@ def lib() -> ctypes.CDLL:
 _NATIVE = None
 
 
+class _Absent:
+    """In the native module's place where there is none for this torch and Python: takes no
+    call, so that every one is made by the Python path below it."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _native():
-    """The native module, loaded once (it links to libprcr.so)."""
+    """The native module, loaded once (it links to libprcr.so), or what stands for it."""
     global _NATIVE
     if _NATIVE is None:
-        lib()
-        _torch()
-        from . import _prcr_native
-        _prcr_native.setup(Rope, Memory, Cache, MODES)
-        _NATIVE = _prcr_native
+        here = "torch {}, Python {}.{}".format(_torch().__version__, *sys.version_info[:2])
+        try:
+            from . import _prcr_native as module
+            built_for = getattr(module, "built_for", "an earlier version")
+            if built_for != here:
+                raise ImportError(f"it was built for {built_for}, this is {here}")
+            module.setup(Rope, Memory, Cache, MODES)
+        except ImportError as e:
+            warnings.warn(f"the native module of the entry points is not used ({e}): every call costs some "
+                          "20 us more of host time; paper_2606_26631_amd/build.py builds it", RuntimeWarning,
+                          stacklevel=3)
+            module = _Absent()
+        _NATIVE = module
     return _NATIVE
 
 

@@ -79,6 +79,7 @@ def _compile_native(verbose: bool) -> str:
     incs = [*include_paths(), sysconfig.get_paths()["include"], rocm]
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-Wall", "-fvisibility=hidden",
            "-D__HIP_PLATFORM_AMD__", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           '-DPRCR_BUILT_FOR="torch {}, Python {}.{}"'.format(torch.__version__, *sys.version_info[:2]),
            f"-I{INCLUDE}", *[a for i in incs for a in ("-isystem", i)],
            "-c", os.path.join(CSRC, NATIVE_SOURCE), "-o", obj]
     if verbose:

@@ -592,5 +592,10 @@ PyMODINIT_FUNC PyInit__prcr_native() {
   g_raw_stream = PyObject_GetAttrString(torch_c, "_cuda_getCurrentRawStream");
   if (g_raw_stream == nullptr) PyErr_Clear();
   Py_DECREF(torch_c);
-  return PyModule_Create(&module);
+  PyObject *m = PyModule_Create(&module);
+  if (m != nullptr && PyModule_AddStringConstant(m, "built_for", PRCR_BUILT_FOR) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
 }
