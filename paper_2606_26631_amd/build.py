@@ -71,13 +71,30 @@ def _link(objs, out: str, verbose: bool) -> None:
     os.replace(tmp, out)
 
 
+def _cxx() -> str:
+    return os.environ.get("CXX", "g++")
+
+
+def _native_lacks() -> str:
+    """What the native module's build does not find here ("" if nothing)."""
+    try:
+        import torch.utils.cpp_extension  # noqa: F401
+    except ImportError as e:
+        return f"torch ({e})"
+    if shutil.which(_cxx()) is None:
+        return f"a host compiler ({_cxx()})"
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        return "Python's headers"
+    return ""
+
+
 def _compile_native(verbose: bool) -> str:
     import torch
     from torch.utils.cpp_extension import include_paths
     obj = os.path.join(BUILD_DIR, os.path.splitext(NATIVE_SOURCE)[0] + ".o")
     rocm = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(hipcc()))), "include")
     incs = [*include_paths(), sysconfig.get_paths()["include"], rocm]
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-Wall", "-fvisibility=hidden",
+    cmd = [_cxx(), "-O2", "-std=c++17", "-fPIC", "-Wall", "-fvisibility=hidden",
            "-D__HIP_PLATFORM_AMD__", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            '-DPRCR_BUILT_FOR="torch {}, Python {}.{}"'.format(torch.__version__, *sys.version_info[:2]),
            f"-I{INCLUDE}", *[a for i in incs for a in ("-isystem", i)],
@@ -93,7 +110,7 @@ def _compile_native(verbose: bool) -> str:
 def _link_native(obj: str, verbose: bool) -> None:
     from torch.utils.cpp_extension import library_paths
     tmp = NATIVE_OUT + ".tmp"
-    cmd = [os.environ.get("CXX", "g++"), "-shared", obj, "-o", tmp, *[f"-L{d}" for d in library_paths()],
+    cmd = [_cxx(), "-shared", obj, "-o", tmp, *[f"-L{d}" for d in library_paths()],
            "-ltorch_python", "-ltorch_cpu", "-lc10", f"-L{PKG}", f"-l:{os.path.basename(OUT)}",
            "-Wl,-rpath,$ORIGIN"]
     if verbose:
@@ -107,14 +124,26 @@ def _link_native(obj: str, verbose: bool) -> None:
 def build(verbose: bool = False) -> str:
     """Compile every source for gfx950 and link libprcr.so, the measurement's reference
     copy kernels into libprcr_copyref.so, and the binding's native module; returns
-    libprcr.so's path."""
+    libprcr.so's path.  The native module is left out, with a line on stderr, where torch, a
+    host compiler or Python's headers are missing: a C program needs only the library, and
+    the binding makes its calls without the module."""
     os.makedirs(BUILD_DIR, exist_ok=True)
+    lacks = _native_lacks()
     with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + len(COPYREF_SOURCES) + 1)) as ex:
-        native = ex.submit(_compile_native, verbose)
+        native = None if lacks else ex.submit(_compile_native, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES + COPYREF_SOURCES))
     _link(objs[:len(SOURCES)], OUT, verbose)
     _link(objs[len(SOURCES):], COPYREF_OUT, verbose)
-    _link_native(native.result(), verbose)
+    made = False
+    try:
+        if native is None:
+            print(f"the binding's native module is not built: {lacks} is missing", file=sys.stderr)
+        else:
+            _link_native(native.result(), verbose)
+            made = True
+    finally:
+        if not made and os.path.exists(NATIVE_OUT):
+            os.remove(NATIVE_OUT)     # no earlier build's module beside a new library
     return OUT
 
 
