@@ -1125,8 +1125,11 @@ bool overlap(const void *a, double na, const void *b, double nb) {
 // takes 18.9 us in one chunk and 23 in two.  But sequences of different lengths are shared
 // out better in more (2,912-6,512 keys: 236 us in one, 216 in two), so where every chunk
 // keeps 512 keys there are two to four rounds of workgroups over the chip (64 sequences of
-// 2,912-6,512 keys, 2 KV heads: 128 us where chunks had to keep 1,024, 115 with 512).  Either way
-// the count that fills its last round best is taken.  A cache that is at most 256 chunks of
+// 2,912-6,512 keys, 2 KV heads: 128 us where chunks had to keep 1,024, 115 with 512).  With one
+// or two heads per KV head a chunk takes as long and a merge less, and 256 do: the longest of
+// 16 sequences (2,007 keys, the others 250; 8 KV heads of one head, D = 64) decides the layer,
+// 15.0 us in the two chunks that 512 allow and 12.4 in four; all of 1,003 keys, 12.0 and 12.9.
+// Either way the count that fills its last round best is taken.  A cache that is at most 256 chunks of
 // 64 keys is read by workgroups of two waves, so that twice as many compute units take part
 // (one sequence of 1,152 keys: 8.4 us a layer with four waves, 7.9 with two; 300 keys: 7.3
 // and 6.7).
@@ -1158,7 +1161,7 @@ void plan_splits(DecodeParams *p, prcr_dtype dtype, bool paged) {
   const int64_t more = most >= std::min(ceil_div(2 * kUnits, pairs), room) ? rounds(2 * kUnits, 4 * kUnits) : fill;
   p->fill = static_cast<int32_t>(fill);
   p->n_split = static_cast<int32_t>(most >= more ? std::max(fill, more) : fill);
-  p->min_keys = kMinKeys;
+  p->min_keys = p->n_q_heads <= 2 * p->n_kv_heads ? kMinKeys / 2 : kMinKeys;
   if (pairs * ceil_div(capacity, 64) <= kUnits) p->waves = 2;
 }
 

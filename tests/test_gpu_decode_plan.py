@@ -1,5 +1,5 @@
 """How decode attention splits a call must not show in its results: lengths on both sides of
-every line of the plan (one chunk or several by the chunk's 512 keys, workgroups of two or
+every line of the plan (one chunk or several by the chunk's 512 or 256 keys, workgroups of two or
 four waves by the cache's capacity, splits without keys), with workgroup counts that do and
 do not fill the chip's 256 compute units, against the float64 oracle.
 
@@ -24,6 +24,8 @@ CASES = [
     (64, 4, 7, 1040, 16, (1022, 1023, 1024, 1025, 1026, 511, 512, 513)),   # one or two chunks of 256
     (40, 4, 2, 1700, 0, (1535, 1536, 1537, 1023, 1025, 200)),              # 160 pairs: uneven rounds
     (33, 6, 8, 1100, 8, (1024, 1025, 1100, 0)),                            # 198 pairs
+    (32, 8, 1, 1100, 0, (511, 512, 513, 1100, 257, 0)),                    # one head: two chunks from 512 keys
+    (16, 8, 2, 2100, 16, (2049, 1023, 1025, 900, 130, 64)),                # two heads: four or two chunks
     (70, 3, 3, 1300, 0, (1200, 1300, 513, 64)),                            # more than 64 sequences
 ]
 
