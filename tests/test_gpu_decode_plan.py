@@ -1,7 +1,8 @@
 """How decode attention splits a call must not show in its results: lengths on both sides of
 every line of the plan (one chunk or several by the chunk's 512 or 256 keys, workgroups of two or
 four waves by the cache's capacity, splits without keys), with workgroup counts that do and
-do not fill the chip's 256 compute units, against the float64 oracle.
+do not fill the chip's 256 compute units, and batches that the workgroups order by length in
+each of the ways they do, against the float64 oracle.
 
 Tolerance: as in test_gpu_attention.py, float32 sums of values of at most max |V|."""
 import numpy as np
@@ -26,7 +27,19 @@ CASES = [
     (33, 6, 8, 1100, 8, (1024, 1025, 1100, 0)),                            # 198 pairs
     (32, 8, 1, 1100, 0, (511, 512, 513, 1100, 257, 0)),                    # one head: two chunks from 512 keys
     (16, 8, 2, 2100, 16, (2049, 1023, 1025, 900, 130, 64)),                # two heads: four or two chunks
-    (70, 3, 3, 1300, 0, (1200, 1300, 513, 64)),                            # more than 64 sequences
+    (70, 3, 3, 1300, 0, (1200, 1300, 513, 64)),                            # more than 64 sequences, one chunk
+    # More than 64 sequences (taken in their own order) in several chunks, with a second
+    # round of workgroups, whose rows go in reverse, inside the grid.
+    (100, 1, 4, 1700, 0, (1700, 1650, 900, 513, 0)),                       # five chunks of 340
+    (70, 3, 7, 1600, 16, (1600, 1537, 1000, 511, 0)),                      # three, the last reversed
+    (130, 2, 4, 2200, 24, (2200, 1600, 1025, 1024, 700)),                  # three, the second reversed
+    # Workgroups of two waves that rank many sequences: up to 32 each wave alone, beyond
+    # that the two waves half of them each; lengths that tie, empty sequences.
+    (17, 1, 4, 900, 0, (900, 900, 513, 0, 0)),
+    (32, 1, 8, 512, 16, (512, 512, 511, 0, 0, 0)),
+    (33, 1, 4, 256, 0, (256, 256, 255, 0, 0, 33, 33)),
+    (40, 1, 7, 256, 8, (256, 256, 130, 0, 0, 33, 33)),
+    (64, 1, 2, 256, 16, (256, 256, 255, 0, 0, 65, 65)),
 ]
 
 
