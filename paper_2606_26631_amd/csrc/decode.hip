@@ -28,37 +28,14 @@
 namespace prcr {
 namespace {
 
-#ifndef PRCR_DEC_ITERS
-#define PRCR_DEC_ITERS 2
-#endif
-#ifndef PRCR_DEC_WAVES
-#define PRCR_DEC_WAVES 4
-#endif
-constexpr int kWaves = PRCR_DEC_WAVES;
-constexpr int kIters = PRCR_DEC_ITERS;   // key rows per lane group in flight
-constexpr int kUnits = 256;              // compute units of the chip
+constexpr int kWaves = 4;    // per workgroup, of the float32 kernel and the merge
+constexpr int kIters = 2;    // float32 kernel: key rows per lane group in flight
+constexpr int kUnits = 256;  // compute units of the chip
 
-template <typename T>
-struct Elems;
-template <>
-struct Elems<float> {
-  static constexpr int kPerChunk = 4;
-  __device__ static __forceinline__ void unpack(u32x4 w, float *x) {
+__device__ __forceinline__ void unpack(u32x4 w, float *x) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) x[q] = __uint_as_float(w[q]);
-  }
-};
-template <>
-struct Elems<uint16_t> {
-  static constexpr int kPerChunk = 8;
-  __device__ static __forceinline__ void unpack(u32x4 w, float *x) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      x[2 * q] = __uint_as_float(w[q] << 16);
-      x[2 * q + 1] = __uint_as_float(w[q] & 0xFFFF0000u);
-    }
-  }
-};
+  for (int q = 0; q < 4; ++q) x[q] = __uint_as_float(w[q]);
+}
 
 // Scores are kept in base-2 units (the query carries log2(e)), so every
 // softmax weight is one hardware exp2.
@@ -75,11 +52,11 @@ __device__ __forceinline__ float dpp(float v) {
 // group ends with the same total: partners add the same two values at each step.
 template <int LPK>
 __device__ __forceinline__ float group_sum(float s) {
-  static_assert(LPK == 8 || LPK == 16 || LPK == 32, "unsupported lane group");
+  static_assert(LPK == 16 || LPK == 32, "unsupported lane group");
   s += dpp<0xB1>(s);                               // quad permutation 1,0,3,2: lane ^ 1
   s += dpp<0x4E>(s);                               // quad permutation 2,3,0,1: lane ^ 2
   s += dpp<0x141>(s);                              // mirror in 8-lane halves: the other quad
-  if constexpr (LPK >= 16) s += dpp<0x140>(s);     // mirror in the 16-lane row: the other half
+  s += dpp<0x140>(s);                              // mirror in the 16-lane row: the other half
   if constexpr (LPK >= 32) s += __shfl_xor(s, 16);
   return s;
 }
@@ -231,13 +208,13 @@ __device__ __forceinline__ void finish_split(const DecodeParams &p, int b, int k
   }
 }
 
-template <typename T, int D, int GT, bool kPaged>
+template <int D, int GT, bool kPaged>
 __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const DecodeParams p) {
-  constexpr int EPL = Elems<T>::kPerChunk;   // elements per lane (one 16-byte chunk)
+  constexpr int EPL = 4;                     // elements per lane (one 16-byte chunk)
   constexpr int LPK = D / EPL;               // lanes per key row
   constexpr int KPW = kWave / LPK;           // key rows per wave per iteration
   constexpr int KPB = kWaves * KPW;          // key rows per workgroup per iteration
-  constexpr int kRowBytes = D * static_cast<int>(sizeof(T));
+  constexpr int kRowBytes = D * static_cast<int>(sizeof(float));
   constexpr int P = D / 2;
   static_assert(LPK >= 2 && kWave % LPK == 0, "unsupported head_dim");
   __shared__ float s_m[kWaves][GT];
@@ -280,8 +257,8 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
       const int qh = kvh * G + (g < G ? g : 0);
       const char *qrow = static_cast<const char *>(p.q) + (static_cast<int64_t>(b) * p.n_q_heads + qh) * kRowBytes;
       float x[EPL], xp[EPL];
-      Elems<T>::unpack(*reinterpret_cast<const u32x4 *>(qrow + c * 16), x);
-      Elems<T>::unpack(*reinterpret_cast<const u32x4 *>(qrow + cp * 16), xp);
+      unpack(*reinterpret_cast<const u32x4 *>(qrow + c * 16), x);
+      unpack(*reinterpret_cast<const u32x4 *>(qrow + cp * 16), xp);
 #pragma unroll
       for (int e = 0; e < EPL; ++e) {
         const double y = first ? static_cast<double>(x[e]) * cs[e] - static_cast<double>(xp[e]) * sn[e]
@@ -362,7 +339,7 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
 #pragma unroll
     for (int u = 0; u < kIters; ++u) {
       float k[EPL];
-      Elems<T>::unpack(kc[u], k);
+      unpack(kc[u], k);
 #pragma unroll
       for (int g = 0; g < GT; ++g) {
         float s = 0.f;
@@ -375,7 +352,7 @@ __global__ __launch_bounds__(kWaves * kWave) void decode_partial_kernel(const De
     // values of rows without weight are taken as zero.
     float v[kIters][EPL];
 #pragma unroll
-    for (int u = 0; u < kIters; ++u) Elems<T>::unpack(live[u] ? vc[u] : u32x4{0u, 0u, 0u, 0u}, v[u]);
+    for (int u = 0; u < kIters; ++u) unpack(live[u] ? vc[u] : u32x4{0u, 0u, 0u, 0u}, v[u]);
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
       float mn = m[g];
@@ -936,6 +913,8 @@ __device__ __forceinline__ float wave_sum(float x) {
 // 1,500-3,000 keys, 4 KV heads of 7, 32 splits), and the same with 3 splits, where launch
 // and one round are all.
 constexpr int kPre = 8;
+constexpr int kMostSplits = 768;             // of any call (decode_splits)
+static_assert(kMostSplits <= 16 * kWave, "the merge has a lane for every split of a wave");
 template <int D, bool kPaged, int kHeadWaves>
 __global__ __launch_bounds__((kHeadWaves > kWaves ? kHeadWaves : kWaves) * kWave) void decode_combine_kernel(
     const DecodeParams p) {
@@ -954,7 +933,7 @@ __global__ __launch_bounds__((kHeadWaves > kWaves ? kHeadWaves : kWaves) * kWave
     return ws + static_cast<int64_t>(min(i * kHeadWaves + part, p.n_split - 1)) * (D + 2);
   };
   const int len_in = p.cache_len[b];
-  float m = split_row(lane)[D], l = split_row(lane)[D + 1];
+  const float m = split_row(lane)[D], l = split_row(lane)[D + 1];   // (at most kWave splits a wave)
   feat o[kPre];
 #pragma unroll
   for (int k = 0; k < kPre; ++k) o[k] = *reinterpret_cast<const feat *>(split_row(k) + F * lane);
@@ -966,34 +945,27 @@ __global__ __launch_bounds__((kHeadWaves > kWaves ? kHeadWaves : kWaves) * kWave
     const int split = i * kHeadWaves + part;
     return split < p.n_split && (split == 0 || p.all_splits || static_cast<int64_t>(split) * chunk < len);
   };
-  float M = -FLT_MAX, L = 0.f;
+  const bool in = written(lane);
+  const int n = __popcll(__ballot(in));
+  const bool valid = in && l != 0.f;         // (a split with a NaN key counts: its NaN reaches L)
+  float M = wave_max(valid ? m : -FLT_MAX);
+  const float w = valid ? exp2_fast(m - M) : 0.f;
+  float L = wave_sum(valid ? l * w : 0.f);
   feat O = {};
-  for (int i0 = 0; written(i0); i0 += kWave) {
-    if (i0 > 0) {
-      m = split_row(i0 + lane)[D];
-      l = split_row(i0 + lane)[D + 1];
+  for (int k0 = 0; k0 < n; k0 += kPre) {
+    if (k0 > 0) {
+#pragma unroll
+      for (int k = 0; k < kPre; ++k) o[k] = *reinterpret_cast<const feat *>(split_row(k0 + k) + F * lane);
+      // All loads before the first use.  Below the breaks, where they sink without this, they
+      // go one by one: 63 splits of 64 keys, 4 KV heads of 7 heads, 11.2 us a layer and not 9.7.
+      asm volatile("" ::: "memory");
     }
-    const bool in = written(i0 + lane);
-    const int n = __popcll(__ballot(in));
-    const bool valid = in && l != 0.f;   // (a split with a NaN key counts: its NaN reaches L)
-    const float mx = fmaxf(M, wave_max(valid ? m : -FLT_MAX));
-    const float corr = exp2_fast(M - mx);
-    M = mx;
-    const float w = valid ? exp2_fast(m - M) : 0.f;
-    L = fmaf(L, corr, wave_sum(valid ? l * w : 0.f));
-    O *= corr;
-    for (int k0 = 0; k0 < n; k0 += kPre) {
-      if (i0 + k0 > 0) {
 #pragma unroll
-        for (int k = 0; k < kPre; ++k) o[k] = *reinterpret_cast<const feat *>(split_row(i0 + k0 + k) + F * lane);
-      }
+    for (int k = 0; k < kPre; ++k) {
+      if (k0 + k >= n) break;
+      const float wk = lane_value(w, k0 + k);
 #pragma unroll
-      for (int k = 0; k < kPre; ++k) {
-        if (k0 + k >= n) break;
-        const float wk = lane_value(w, k0 + k);
-#pragma unroll
-        for (int f = 0; f < F; ++f) O[f] = fmaf(o[k][f], wk, O[f]);
-      }
+      for (int f = 0; f < F; ++f) O[f] = fmaf(o[k][f], wk, O[f]);
     }
   }
   if constexpr (kHeadWaves > 1) {
@@ -1048,7 +1020,7 @@ void launch_bf16(const DecodeParams &p, hipStream_t stream) {
 template <typename T, int D, int GT, bool kPaged>
 hipError_t launch_split(const DecodeParams &in, hipStream_t stream) {
   DecodeParams p = in;
-  // Keys a workgroup's waves take at once: a tile each, or kWave / (D / chunk) rows each.
+  // Keys a workgroup's waves take at once: a tile each, or kWave / (D / 4) rows each.
   if constexpr (std::is_same_v<T, uint16_t>) {
     p.round = p.waves * kTile;
     if (p.waves == 2)
@@ -1056,8 +1028,8 @@ hipError_t launch_split(const DecodeParams &in, hipStream_t stream) {
     else
       launch_bf16<D, GT, kPaged, 4>(p, stream);
   } else {
-    p.round = kWaves * (kWave / (D / Elems<T>::kPerChunk));
-    decode_partial_kernel<T, D, GT, kPaged>
+    p.round = kWaves * (kWave / (D / 4));
+    decode_partial_kernel<D, GT, kPaged>
         <<<dim3(p.n_split, p.n_kv_heads, p.batch), kWaves * kWave, 0, stream>>>(p);
   }
   hipError_t e = hipGetLastError();
@@ -1096,7 +1068,7 @@ int decode_splits(int64_t capacity, int batch, int n_kv_heads, int group) {
   // Partials that a call has room for.  As many workgroups as the chip holds at once:
   // 256 compute units with 3 workgroups each (2 with 8 query heads per KV head, whose
   // bf16 kernel holds more registers).  No split of fewer than 64 keys at full capacity.
-  const int64_t target = group > 4 ? 512 : 768;
+  const int64_t target = group > 4 ? 512 : kMostSplits;
   const int64_t pairs = static_cast<int64_t>(batch) * n_kv_heads;
   int64_t ns = (target + pairs - 1) / pairs;
   const int64_t most = (capacity + 63) / 64;
