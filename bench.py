@@ -665,28 +665,28 @@ def decode_attention_bw(dev, steps=20, cfg=3):
     mean_s = sum(ms) / len(ms) / 1e3
     nbytes = int(lens.sum()) * w.H * w.D * 2 * 2 + w.B * Hq * w.D * (2 + 4)
     # The same K and V reads with no arithmetic (copyref decode_read_kernel), on the
-    # same cache, with the decode kernel's split and lane layout, one layer per call
-    # in the same order as above.
+    # same cache, with the decode kernel's tiles and lane layout, one layer per call
+    # in the same order as above: each sequence in one to four chunks, the fastest taken.
     L = copyref_lib()
-    per_split = w.B * Hq * (w.D + 2) * 4
-    n_split = prcr.decode_workspace_bytes(cache, w.B, Hq) // per_split
-    sink = torch.empty(w.B * w.H * n_split, dtype=torch.int32, device=dev)
+    sink = torch.empty(w.B * w.H * 4, dtype=torch.int32, device=dev)
     cc = cache.to_c()
 
-    calls = [0]
+    def time_reads(n_split):
+        calls = [0]
 
-    def read_pattern():
-        layer = calls[0] % w.NL
-        calls[0] += 1
-        rc = L.prcr_copyref_decode_read(cache.k.data_ptr(), cache.v.data_ptr(),
-                                        cache.block_table.data_ptr() if w.paged else None,
-                                        cl.data_ptr(), sink.data_ptr(), w.B, w.NL, w.H, layer,
-                                        cc.s_max, cc.block_size, cc.max_blocks, cc.n_blocks,
-                                        n_split, int(w.paged), s.cuda_stream)
-        if rc != 0:
-            raise RuntimeError(f"prcr_copyref_decode_read failed ({rc})")
+        def read_pattern():
+            layer = calls[0] % w.NL
+            calls[0] += 1
+            rc = L.prcr_copyref_decode_read(cache.k.data_ptr(), cache.v.data_ptr(),
+                                            cache.block_table.data_ptr() if w.paged else None,
+                                            cl.data_ptr(), sink.data_ptr(), w.B, w.NL, w.H, layer,
+                                            cc.s_max, cc.block_size, cc.max_blocks, cc.n_blocks,
+                                            n_split, int(w.paged), s.cuda_stream)
+            if rc != 0:
+                raise RuntimeError(f"prcr_copyref_decode_read failed ({rc})")
+        return _timed(read_pattern, s, steps, 3)[0]
 
-    read_ms, _ = _timed(read_pattern, s, steps, 3)
+    read_ms, n_split = min((time_reads(n), n) for n in (1, 2, 3, 4))
     read_bytes = int(lens.sum()) * w.H * w.D * 2 * 2
     del cache, ws, sink
     torch.cuda.empty_cache()
@@ -698,7 +698,8 @@ def decode_attention_bw(dev, steps=20, cfg=3):
            "unit": "GB/s", "frac": round(nbytes / mean_s / 1e9 / HBM_PEAK_GBS, 4)}
     read_gbs = read_bytes / (read_ms / 1e3) / 1e9
     res["pattern_read"] = {"kernel": "copyref decode_read_kernel (the same K/V reads, no "
-                                     "arithmetic)", "mean_launch_us": round(read_ms * 1e3, 2),
+                                     "arithmetic)", "chunks_per_sequence": n_split,
+                           "mean_launch_us": round(read_ms * 1e3, 2),
                            "bytes": read_bytes, "achieved": round(read_gbs, 1), "unit": "GB/s",
                            "frac": round(read_gbs / HBM_PEAK_GBS, 4)}
     res["frac_of_pattern"] = round(res["achieved"] / read_gbs, 4)

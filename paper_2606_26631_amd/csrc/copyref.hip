@@ -6,8 +6,9 @@
 //                         the attainable read + write rate of the GPU.
 //   prcr_copyref_decode_read  decode attention's reads with no arithmetic: every K and
 //                         V row of one layer's attended slots, with the bf16
-//                         decode kernel's split of each sequence over workgroups,
-//                         tiles, lane layouts and loads in flight.
+//                         decode kernel's tiles, lane layouts, loads in flight and
+//                         order of workgroups (four waves each), each sequence split
+//                         evenly over as many workgroups as the caller says.
 //   prcr_copyref_prefill  prefill capture's access pattern with no arithmetic: one
 //                         layer's raw K/V rows of every prompt token to the
 //                         contiguous cache at slot s, and visual tokens' rows to the
@@ -23,8 +24,7 @@
 //                         batch in flight) and dispatch order (token fastest, then
 //                         row group, then the key array before the value array).
 //
-// They use 16-byte non-temporal loads and stores, as the rebind does (the decode
-// read's key loads are plain, as in the decode kernel).  Offsets
+// They use 16-byte non-temporal loads and stores, as the kernels do.  Offsets
 // are byte offsets computed by the caller, who checks them against the arrays.
 #include <hip/hip_runtime.h>
 
@@ -145,111 +145,139 @@ struct DecodeReadParams {
   const char *v;               // cache values
   const int32_t *block_table;  // paged: [batch][max_blocks]
   const int32_t *len;          // [batch] attended slots
-  uint32_t *out;               // [gridDim.z][gridDim.y][gridDim.x] one word per workgroup
+  uint32_t *out;               // [batch][n_kv_heads][n_split] one word per workgroup
   int32_t n_layers, n_kv_heads, layer, s_max, block_size, max_blocks, n_blocks, n_split, paged;
 };
 
-// One workgroup per (split, KV head, sequence), as the decode kernel launches them
-// (sequences taken longest first), with the bf16 decode kernel's accesses.  Rows are 256 bytes (head_dim 128, bf16).
-// The sequence's keys are split in whole rounds of 64 keys; a wave takes tiles of
-// 16 keys 64 keys apart.  Key rows are read in the matrix-product operand layout
-// (lane l: row l % 16, 16-byte chunks l / 16 + 4 * kk, plain loads), value rows 16
-// lanes to a row (non-temporal loads); one buffer of each, the next tile's keys
-// loaded once this tile's keys are used and its values once this tile's values
-// are.  Paged caches whose blocks are whole tiles take one block-table entry per
-// tile from a per-wave register filled 64 tiles at a time; others read an entry
-// per key.  Keys past the chunk (or in a block outside the pool) read the head's
-// first row, as in the decode kernel.  The words read are folded into one value
-// per workgroup so that the loads are kept.
-template <bool kPaged, bool kTileBlocks>
+// One workgroup of four waves per (KV head, sequence, split), splits outermost, with the
+// bf16 decode kernel's accesses.  Rows are 256 bytes (head_dim 128, bf16).  At most 64
+// sequences are taken longest first, in reverse in every second round of 256 workgroups.
+// The sequence's keys are split in whole rounds of 128 keys; a wave takes tiles of 32
+// keys 128 keys apart.  Key loads take whole cache lines of 8 rows, value loads 4 whole
+// rows; one buffer of each, the next tile's keys loaded once this tile's keys are used and
+// its values once this tile's values are.  Paged caches read a block-table entry per key, two
+// tiles ahead: one base per 16 keys where the block size is a multiple of 16, else a row
+// per key.  Keys past the chunk (or in a block outside the pool) read a row that exists and
+// are left out of the result: the exclusive or of the words read, one value per workgroup.
+template <bool kPaged, bool kHalfBlocks>
 __global__ __launch_bounds__(kThreads) void decode_read_kernel(const DecodeReadParams p) {
-  constexpr int kRowBytes = 256, kTile = 16, KPB = 64, KK = 4, VL = 4, KPW = 4;
-  const int split = blockIdx.x, kvh = blockIdx.y;
+  constexpr int kRowBytes = 256, kTile = 32, KPB = 128, kUnits = 256;
+  const int split = blockIdx.z, kvh = blockIdx.x;
   const int lane = threadIdx.x & 63;
-  // Rows of workgroups go to the sequences longest first, as in the decode kernel.
-  int b = blockIdx.z;
-  if (gridDim.z <= 64) {
-    const int nb = static_cast<int>(gridDim.z);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n16 = lane % 16, kj = lane / 16;
+  const int nb = static_cast<int>(gridDim.y);
+  const uint32_t before = static_cast<uint32_t>(split) * gridDim.x * gridDim.y;
+  int b = (before / kUnits) & 1 ? nb - 1 - static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y);
+  if (nb <= 64) {
     const int mine = lane < nb ? max(p.len[lane], 0) : -1;
     int rank = 0;
     for (int i = 0; i < nb; ++i) {
       const int other = __builtin_amdgcn_readlane(mine, i);
       rank += (other > mine) || (other == mine && i < lane);
     }
-    const unsigned long long hit = __ballot(lane < nb && rank == static_cast<int>(blockIdx.z));
+    const unsigned long long hit = __ballot(lane < nb && rank == b);
     b = hit ? __ffsll(static_cast<long long>(hit)) - 1 : b;
   }
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int kt = lane % kTile, kj = lane / kTile;
-  const int vr = lane / 16, vc = lane % 16;
-  // lengths clamped to the capacity, and block-table entries outside the pool
-  // read the head's first row instead, as in the decode kernel: every access stays
-  // inside the arrays whatever the inputs
+  // Lengths clamped to the capacity: every access stays inside the arrays whatever the inputs.
   const int64_t cap = kPaged ? static_cast<int64_t>(p.max_blocks) * p.block_size : p.s_max;
   const int len = static_cast<int>(min(max(static_cast<int64_t>(p.len[b]), int64_t{0}), cap));
   const int per = (len + p.n_split - 1) / p.n_split;
-  const int chunk = (per + KPB - 1) / KPB * KPB;
-  const int j0 = min(len, split * chunk), j1 = min(len, j0 + chunk);
-  const int64_t row_base =
-      kPaged ? 0 : ((static_cast<int64_t>(b) * p.n_layers + p.layer) * p.n_kv_heads + kvh) * p.s_max;
-  const int64_t row_any =
-      kPaged ? static_cast<int64_t>(p.layer) * p.n_blocks * p.block_size * p.n_kv_heads + kvh : row_base;
-  auto table = [&](int j) -> int32_t {
-    const int js = j < j1 ? j : 0;
-    return p.block_table[static_cast<int64_t>(b) * p.max_blocks + js / p.block_size];
+  const int64_t chunk = (static_cast<int64_t>(per) + KPB - 1) / KPB * KPB;
+  const int j0 = static_cast<int>(min(static_cast<int64_t>(len), split * chunk));
+  const int j1 = static_cast<int>(min(static_cast<int64_t>(len), j0 + chunk));
+  uint32_t *const out = p.out + (static_cast<int64_t>(b) * p.n_kv_heads + kvh) * p.n_split + split;
+  if (j0 >= j1) {
+    if (threadIdx.x == 0) *out = 0;
+    return;
+  }
+  const int64_t row_layer = static_cast<int64_t>(p.layer) * p.n_blocks * p.block_size;   // paged
+  const int64_t row_any = kPaged ? row_layer * p.n_kv_heads + kvh
+                                 : ((static_cast<int64_t>(b) * p.n_layers + p.layer) * p.n_kv_heads + kvh) * p.s_max;
+  // Slot in the pool of key lane % 32 of the tile at tb, or -1.
+  auto slot_of = [&](int tb) -> int64_t {
+    if constexpr (!kPaged) return 0;
+    const int j = tb + lane % kTile, js = j < j1 ? j : 0, lb = js / p.block_size;
+    const int32_t blk = p.block_table[static_cast<int64_t>(b) * p.max_blocks + lb];
+    return j < j1 && blk >= 0 && blk < p.n_blocks
+               ? static_cast<int64_t>(blk) * p.block_size + (js - lb * p.block_size) : -1;
   };
-  // Rows selected without branches, as in the decode kernel.
-  auto row_of = [&](int tb, int j, int lim, int32_t tile_blk) -> int64_t {
+  struct Rows {
+    int64_t base[2];
+    int last[2];
+    int slot;
+    uint32_t live;
+  };
+  auto rows_of = [&](int tb, int64_t slot) -> Rows {
+    Rows t{};
+    const int n_in = min(max(j1 - tb, 0), kTile);
+    t.live = n_in >= kTile ? ~0u : (1u << n_in) - 1u;
     if constexpr (!kPaged) {
-      return j < lim ? row_base + j : row_any;
+      const int tc = min(tb, j1 - 1);
+      t.base[0] = row_any + tc;
+      t.last[0] = j1 - 1 - tc;
     } else {
-      const int32_t blk = kTileBlocks ? tile_blk : table(j);
-      const int off = kTileBlocks ? (tb % p.block_size) + (j - tb) : j % p.block_size;
-      const int64_t row =
-          ((static_cast<int64_t>(p.layer) * p.n_blocks + blk) * p.block_size + off) * p.n_kv_heads + kvh;
-      return j < lim && blk >= 0 && blk < p.n_blocks ? row : row_any;
+      t.live = static_cast<uint32_t>(__ballot(slot >= 0));   // lanes t and t + 32 agree
+      if constexpr (kHalfBlocks) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t lh = (t.live >> (16 * h)) & 0xFFFFu;
+          const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(slot), 16 * h);
+          const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(slot >> 32), 16 * h);
+          const int64_t first = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+          t.base[h] = lh != 0 ? (row_layer + first) * p.n_kv_heads + kvh : row_any;
+          t.last[h] = lh != 0 ? __popc(lh) - 1 : 0;
+        }
+      } else {
+        t.slot = slot >= 0 ? static_cast<int>(slot) : 0;
+      }
     }
+    return t;
+  };
+  const uint32_t step = kPaged ? static_cast<uint32_t>(p.n_kv_heads) * kRowBytes : kRowBytes;
+  auto offset = [&](const Rows &t, int key, int half) -> int64_t {
+    if constexpr (!kPaged)
+      return t.base[0] * kRowBytes + static_cast<uint32_t>(min(key, t.last[0])) * step;
+    else if constexpr (kHalfBlocks)
+      return t.base[half] * kRowBytes + static_cast<uint32_t>(min(key - 16 * half, t.last[half])) * step;
+    else
+      return (row_layer + static_cast<int64_t>(static_cast<uint32_t>(__shfl(t.slot, key)))) * step +
+             static_cast<int64_t>(kvh) * kRowBytes;
+  };
+  // Key of load (st, kk): line kk / 2 of the rows of product columns 0..7 (kk even) or 8..15.
+  auto key_of = [&](int st, int kk) -> int { return 8 * (n16 % 8 / 4) + n16 % 4 + 4 * st + 16 * (kk % 2); };
+  auto load_k = [&](const Rows &t, u32x4 (&kd)[2][4]) {
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        kd[st][kk] = ld(p.k + offset(t, key_of(st, kk), kk % 2) + (n16 / 8) * 64 + kj * 16 + kk / 2 * 128);
+  };
+  auto load_v = [&](const Rows &t, u32x4 (&vd)[8]) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) vd[u] = ld(p.v + offset(t, 4 * u + kj, u / 4) + n16 * 16);
   };
   uint32_t acc = 0;
+  auto fold = [&](u32x4 w, bool in) { acc ^= in ? w.x ^ w.y ^ w.z ^ w.w : 0u; };
   const int jw = j0 + wave * kTile;
-  const int n_tiles = jw < j1 ? (j1 - jw + KPB - 1) / KPB : 0;
-  const int rounds = kTileBlocks ? (n_tiles + 63) / 64 : (n_tiles > 0 ? 1 : 0);
-  for (int r = 0; r < rounds; ++r) {
-    const int n0 = r * 64;
-    int32_t tab = 0;
-    if constexpr (kTileBlocks) tab = table(jw + (n0 + lane) * KPB);
-    const int lim = kTileBlocks ? static_cast<int>(min(static_cast<int64_t>(j1),
-                                                       static_cast<int64_t>(jw) + static_cast<int64_t>(n0 + 64) * KPB))
-                                : j1;
-    auto blk_of = [&](int n) -> int32_t {
-      if constexpr (kTileBlocks) return __builtin_amdgcn_readlane(tab, min(n - n0, 63));
-      return 0;
-    };
-    auto load_k = [&](int tb, int32_t blk, u32x4 *kd) {
-      const char *kp = p.k + row_of(tb, tb + kt, lim, blk) * kRowBytes + kj * 16;
+  u32x4 kr[2][4], vv[8];
+  const int64_t s0 = slot_of(jw);
+  int64_t s_next = slot_of(jw + KPB);
+  Rows t = rows_of(jw, s0);
+  load_k(t, kr);
+  load_v(t, vv);
+  for (int jt = jw; jt < j1; jt += KPB) {
+    const uint32_t live = t.live;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kd[kk] = *reinterpret_cast<const u32x4 *>(kp + kk * 64);
-    };
-    auto load_v = [&](int tb, int32_t blk, u32x4 *vd) {
+    for (int st = 0; st < 2; ++st)
 #pragma unroll
-      for (int u = 0; u < VL; ++u) vd[u] = ld(p.v + row_of(tb, tb + KPW * u + vr, lim, blk) * kRowBytes + vc * 16);
-    };
-    u32x4 kr[KK], vv[VL];
-    int n = n0, jt = jw + n0 * KPB;
-    int32_t blk = blk_of(n);
-    load_k(jt, blk, kr);
-    load_v(jt, blk, vv);
-    while (jt < lim) {
-      const int32_t blk_n = blk_of(n + 1);
+      for (int kk = 0; kk < 4; ++kk) fold(kr[st][kk], (live >> key_of(st, kk)) & 1u);
+    t = rows_of(jt + KPB, s_next);
+    s_next = slot_of(jt + 2 * KPB);
+    load_k(t, kr);
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) acc ^= kr[kk].x ^ kr[kk].y ^ kr[kk].z ^ kr[kk].w;
-      load_k(jt + KPB, blk_n, kr);
-#pragma unroll
-      for (int u = 0; u < VL; ++u) acc ^= vv[u].x ^ vv[u].y ^ vv[u].z ^ vv[u].w;
-      load_v(jt + KPB, blk_n, vv);
-      jt += KPB;
-      ++n;
-    }
+    for (int u = 0; u < 8; ++u) fold(vv[u], (live >> (4 * u + kj)) & 1u);
+    load_v(t, vv);
   }
   for (int o = 32; o > 0; o >>= 1) acc ^= __shfl_xor(acc, o);
   __shared__ uint32_t s_acc[kThreads / 64];
@@ -258,7 +286,7 @@ __global__ __launch_bounds__(kThreads) void decode_read_kernel(const DecodeReadP
   if (threadIdx.x == 0) {
     uint32_t a = 0;
     for (int w = 0; w < kThreads / 64; ++w) a ^= s_acc[w];
-    p.out[(static_cast<int64_t>(b) * gridDim.y + kvh) * gridDim.x + split] = a;
+    *out = a;
   }
 }
 
@@ -350,16 +378,21 @@ int prcr_copyref_pattern(const void *src_k, const void *src_v, void *dst_k, void
 }
 
 // Decode attention's reads of one layer (see above): n_split workgroups per
-// (sequence, KV head); out holds batch * n_kv_heads * n_split words.
+// (sequence, KV head); out holds batch * n_kv_heads * n_split words.  Capacities are below
+// 2^30 slots and a pool below 2^31, as decode attention's own.
 int prcr_copyref_decode_read(const void *k, const void *v, const int32_t *block_table,
                              const int32_t *len, uint32_t *out, int32_t batch, int32_t n_layers,
                              int32_t n_kv_heads, int32_t layer, int32_t s_max, int32_t block_size,
                              int32_t max_blocks, int32_t n_blocks, int32_t n_split, int32_t paged,
                              hipStream_t stream) {
   if (k == nullptr || v == nullptr || len == nullptr || out == nullptr || batch < 1 ||
-      batch > 65535 || n_kv_heads < 1 || n_kv_heads > 65535 || n_split < 1 || layer < 0 ||
-      layer >= n_layers || (paged && (block_table == nullptr || block_size < 1 || max_blocks < 1 ||
-                                      n_blocks < 1)) || (!paged && s_max < 1))
+      batch > 65535 || n_kv_heads < 1 || n_kv_heads > 65535 || n_split < 1 || n_split > 65535 ||
+      layer < 0 || layer >= n_layers || (paged && (block_table == nullptr || block_size < 1 ||
+                                                   max_blocks < 1 || n_blocks < 1)) || (!paged && s_max < 1))
+    return 1;
+  constexpr int64_t kMostSlots = int64_t{1} << 30;
+  if ((paged ? static_cast<int64_t>(max_blocks) * block_size : s_max) >= kMostSlots ||
+      (paged && static_cast<int64_t>(n_blocks) * block_size >= 2 * kMostSlots))
     return 1;
   DecodeReadParams p{};
   p.k = static_cast<const char *>(k);
@@ -376,7 +409,7 @@ int prcr_copyref_decode_read(const void *k, const void *v, const int32_t *block_
   p.n_blocks = n_blocks;
   p.n_split = n_split;
   p.paged = paged;
-  const dim3 grid(n_split, n_kv_heads, batch);
+  const dim3 grid(n_kv_heads, batch, n_split);
   if (!paged)
     decode_read_kernel<false, false><<<grid, dim3(kThreads), 0, stream>>>(p);
   else if (block_size % 16 == 0)

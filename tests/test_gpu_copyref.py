@@ -96,3 +96,40 @@ def test_prefill_pattern_copy_writes_the_prefills_rows():
                 exp[3][b, m, layer] = raw_v[b, s]
     for got, want in zip((ck, cv, mk, mv), exp):
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("bs,n_split,B", [(0, 1, 5), (0, 3, 70), (16, 2, 5), (16, 4, 70), (24, 3, 5)])
+def test_decode_read_reads_the_attended_rows(bs, n_split, B):
+    """The decode reads' result is the exclusive or of every word of every attended K and V
+    row of the layer, each read once."""
+    H, D, NL, layer, cap = 3, 128, 2, 1, 1000
+    rng = np.random.default_rng(B + bs)
+    lens = rng.integers(0, cap + 1, B).astype(np.int32)
+    lens[:5] = (cap, 0, 1, 33, 128)
+    word = lambda *s: torch.from_numpy(rng.integers(0, 2 ** 32, s, dtype=np.uint32).view(np.int32))
+    if bs:
+        per = -(-cap // bs)
+        table = rng.permutation(B * per).astype(np.int32).reshape(B, per)
+        k, v = word(NL, B * per, bs, H, D // 2), word(NL, B * per, bs, H, D // 2)
+        rows = lambda x, b, h, n: x[layer, table[b]].reshape(per * bs, H, -1)[:n, h]
+        args = (cap, bs, per, B * per)
+    else:
+        table = None
+        k, v = word(B, NL, H, cap, D // 2), word(B, NL, H, cap, D // 2)
+        rows = lambda x, b, h, n: x[b, layer, h, :n]
+        args = (cap, 0, 0, 0)
+    print(f"decode reads: block {bs}, {n_split} chunks, {B} sequences", flush=True)
+    kd, vd, ld = k.to(DEV), v.to(DEV), to_dev(lens)
+    td = None if table is None else to_dev(table)
+    out = torch.full((B, H, n_split), 77, dtype=torch.int32, device=DEV)
+    assert bench.copyref_lib().prcr_copyref_decode_read(
+        kd.data_ptr(), vd.data_ptr(), None if td is None else td.data_ptr(), ld.data_ptr(), out.data_ptr(), B, NL,
+        H, layer, *args, n_split, int(bool(bs)), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    got = np.bitwise_xor.reduce(out.cpu().numpy(), axis=2)
+    for b in range(B):
+        for h in range(H):
+            want = 0
+            for x in (k, v):
+                want ^= int(np.bitwise_xor.reduce(rows(x, b, h, int(lens[b])).numpy().ravel())) if lens[b] else 0
+            assert int(got[b, h]) == want, (b, h)
