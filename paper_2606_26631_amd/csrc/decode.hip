@@ -661,13 +661,14 @@ __global__ __launch_bounds__(kWaves * kWave, GT == 8 && D == 128 ? 2 : 3) void d
                  row_step + static_cast<int64_t>(kvh) * kRowBytes;
   };
   // Key rows.  The product's operand layout would read a half of each of 16 rows' cache
-  // lines per load, and the other halves with the next one; with more than two waves a
-  // compute unit has more lines in flight than its L1 holds, and halves are read again.
-  // So a load reads whole lines of 8 rows, once, past the caches: line q of the keys of
-  // columns 0..7 by load 2 q, of columns 8..15 by load 2 q + 1, one half of a line in the
-  // lanes of its own column and the other 8 lanes away (swap_rows8 brings it over).  Two
-  // layers of 64 paged sequences of 2,912-6,512 keys (7 heads): 240.4 us in half lines,
-  // 224.4 in whole ones; 32 contiguous ones of 2,756-4,256 keys (4 heads): 155.6 and 151.7.
+  // lines per load, and the other halves with the next one, through the caches.  So a load
+  // reads whole lines of 8 rows, once, past the caches: line q of the keys of columns 0..7
+  // by load 2 q, of columns 8..15 by load 2 q + 1, one half of a line in the lanes of its
+  // own column and the other 8 lanes away (swap_rows8 brings it over).  Two layers of 64
+  // paged sequences of 2,912-6,512 keys (7 heads): 240.4 us in half lines, 224.4 in whole
+  // ones; 32 contiguous ones of 2,756-4,256 keys (4 heads): 155.6 and 151.7.  The counters do
+  // not say why: in half lines the L1 asks the L2 for 0.6 and 1.0 % more lines, and the bytes
+  // from memory are the same.
   const int ka = 8 * (n16 % 8 / 4) + n16 % 4;
   auto load_k = [&](const TileRows &tr, u32x4 (&kd)[2][KK]) {
 #pragma unroll
@@ -1104,7 +1105,9 @@ bool overlap(const void *a, double na, const void *b, double nb) {
 // Either way the count that fills its last round best is taken.  A cache that is at most 256 chunks of
 // 64 keys is read by workgroups of two waves, so that twice as many compute units take part
 // (one sequence of 1,152 keys: 8.4 us a layer with four waves, 7.9 with two; 300 keys: 7.3
-// and 6.7).
+// and 6.7).  The launcher does not know the lengths, so it is the capacity that decides: the
+// same sequence takes 7.1 us in a cache of up to 2,048 slots and 7.7 in a larger one, whose
+// workgroups take four waves' tiles each.
 void plan_splits(DecodeParams *p, prcr_dtype dtype, bool paged) {
   const int64_t room = p->n_split, pairs = static_cast<int64_t>(p->batch) * p->n_kv_heads;
   const int64_t capacity = paged ? static_cast<int64_t>(p->max_blocks) * p->block_size : p->s_max;

@@ -145,7 +145,7 @@ struct DecodeParams {
   int32_t n_split;                // workgroups per (sequence, KV head); room for as many until the launcher's plan
   int32_t fill;                   // splits that give every compute unit a workgroup (this and the rest: the launcher)
   int32_t min_keys;               // keys a chunk has at least where there are more splits than that
-  uint32_t split_inverse, fill_inverse;   // ceil(2^32 / n) of n_split and fill: no divisions on the device
+  uint32_t split_inverse, fill_inverse;   // ceil(2^32 / n) of n_split and fill: chunks without a division
   int32_t group;                  // query heads per KV head
   int32_t waves;                  // waves per workgroup of the bf16 kernel: 2 or 4
   int32_t round;                  // keys per workgroup come in multiples of this

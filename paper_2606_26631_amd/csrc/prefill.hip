@@ -9,8 +9,7 @@
 // (sequence, token, head) rows of the layer (8 at bf16, d 128: one token's 8
 // heads); a lane owns one 16-byte chunk of each half of a row, as in the rebind
 // kernel.  A wave moves one batch of rows, so its latency is mostly the chain of
-// dependent loads before its stores: the kernel keeps that chain at two rounds
-// (three for a paged destination).
+// dependent loads before its stores: the kernel keeps that chain at two rounds.
 #include <climits>
 #include <cmath>
 
@@ -59,9 +58,11 @@ __global__ __launch_bounds__(kWaves * kWave) void prefill_capture_kernel(const P
   // this lane's rotary frequency.  Vector loads complete in issue order, so a load
   // issued only after another's value is used waits a round trip more.
   // Rows are split into sequence, token and head by multiplications: the two 64-bit
-  // divisions were as many instructions as the rotation.  One sequence of 2,560 tokens
-  // took 7.8 us and takes 7.4, 8 of them with 2 KV heads 16.6 and 14.7, with 8 KV heads
-  // 52.5 and 50.4; six of 1,661-2,545 tokens in a paged cache 20.0, as before.
+  // divisions were as many instructions as the rotation.  With them (and the table entry in a
+  // round of its own) and without, medians over twelve allocations, five sets of inputs in
+  // turn: 8 sequences of 2,560 tokens with 2 KV heads 17.1 and 15.9 us; one of 2,129 in a
+  // paged cache with 4 KV heads 7.2 and 6.8, six of 1,783-2,474 the same (20.5 and 20.6).  8
+  // sequences with 8 KV heads are bound by memory: 46.0 (42-53) and 43.0 (42-47).
   int rb[kIters], rs[kIters], rh[kIters];
   int32_t nt[kIters], cst[kIters];
   int64_t Rc[kIters];

@@ -1,11 +1,10 @@
 """GPU parity of decode attention where one workgroup takes a whole sequence
 (one split per sequence and KV head: batch x KV heads at least the number of
-workgroups the library aims for) and a wave takes more than 64 tiles of 16 keys,
-so that paged caches read their block-table entries in several rounds: contiguous
-caches, paged caches whose blocks are whole tiles (16, 48) and paged caches read
-an entry per key (8, 24), with 4 and 8 query heads per KV head.  The oracle checks
-every long sequence and a sample of the short ones.  Tolerance as in
-test_gpu_attention.py."""
+workgroups the library has room for) and a wave takes 32 to 97 tiles of 32 keys:
+contiguous caches, paged caches with a base per 16 keys (blocks of 16, 48) and
+paged caches read an entry per key (8, 24), with 4 and 8 query heads per KV head.
+The oracle checks every long sequence and a sample of the short ones.  Tolerance as
+in test_gpu_attention.py."""
 import numpy as np
 import pytest
 import torch

@@ -102,9 +102,10 @@ def test_outputs_are_kept_until_the_current_stream_has_read_them(route, side):
     assert all(torch.equal(o, others[0]) for o in others)
 
 
-def test_revisit_outputs_on_a_side_stream(route, side):
+@pytest.mark.parametrize("n", [12, 0])
+def test_revisit_outputs_on_a_side_stream(route, side, n):
     torch_side, stream = side
-    M, n = 64, 12
+    M = 64
     ints = lambda a: torch.tensor(a, dtype=torch.int32, device="cuda")
     rows = torch.randn(1, M, 2, H, D, device="cuda")
     mem = prcr.Memory(rows, rows.clone(), ints([[[0, m // 8, m % 8] for m in range(M)]]), ints([M]))
@@ -118,7 +119,7 @@ def test_revisit_outputs_on_a_side_stream(route, side):
             _busy(torch_side)
         outs = prcr.revisit(rope, mem, off, idx, p_txt, cache, lens, stream=stream)
         # Blocks of the outputs' sizes on the current stream, written at once.
-        blocks = [torch.full((s,), -7, dtype=torch.int64, device="cuda") for s in (1, 3 * n, n) for _ in range(4)]
+        blocks = [torch.full((s,), -7, dtype=torch.int64, device="cuda") for s in (1, 3 * n + 1, n + 1) for _ in range(4)]
         torch.cuda.synchronize()
         assert all((b == -7).all() for b in blocks)
         return [*outs, cache.k, cache.v]
